@@ -189,7 +189,7 @@ enum ckpt_section {
     CKPT_SEC_DENSE = 5,     /* DEVICE pointer, data_bytes: allocation k at off_k, the   */
                             /* pad of non-ZERO chunks zero; a ZERO chunk's bytes (and   */
                             /* its pad) are unspecified, read them as zeros (the pack   */
-                            /* with one wave per chunk does not store ZERO chunks)      */
+                            /* of chunks of at most 4 KiB does not store ZERO chunks)   */
                             /* (with CKPT_KEEP_DENSE or CKPT_NO_DRAIN)                  */
     CKPT_SEC_ADDRS = 6      /* host, uint64_t[n_allocs]: device address of allocation k */
                             /* when the image was taken (0 if loaded from version-1     */

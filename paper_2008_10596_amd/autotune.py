@@ -4,8 +4,8 @@ Sweeps chunk size C, waves per chunk W, workgroup size and the load/store
 hint (non-temporal or regular) on the caller's own contexts' allocations, timing the device part of one batched checkpoint (the
 replayed graph: table upload, size scan, chunk map, fused pack + CRC + flags)
 with the image kept in HBM; the best shape is the fastest.  Each trial also
-reports GB/s of the bytes its kernel form moves (one wave per chunk leaves ZERO
-chunks unwritten; several waves per chunk write every chunk).  For every C, every (W, block) must give the
+reports GB/s of the bytes its kernel form moves (one wave per chunk of at most
+4 KiB leaves ZERO chunks unwritten; the other forms write every chunk).  For every C, every (W, block) must give the
 same CRC and flag arrays -- the launch shape may not change a result -- or
 the tuner raises.  Results are cached by device and by a coarse signature of
 the workload (context count, total bytes and median allocation size, each
@@ -119,7 +119,7 @@ def tune(alloc_sets, chunks=DEFAULT_CHUNKS, waves=DEFAULT_WAVES, blocks=DEFAULT_
                         for im in imgs:
                             im.close()
                     t = statistics.median(ms)
-                    alg = live + (stored if W == 1 else dense) + 5 * N
+                    alg = live + (stored if W == 1 and C <= 4096 else dense) + 5 * N
                     trial = {"chunk_bytes": C, "waves_per_chunk": W, "block_threads": B, "load_hint": H,
                              "device_ms": round(t, 4), "gbps": round(alg / (t * 1e-3) / 1e9, 2),
                              "wall_ms": round(wall, 3)}

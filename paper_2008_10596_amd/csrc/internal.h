@@ -146,7 +146,7 @@ struct ChunkArgs {
                               // chunk is written as zeros and checked against it
                               // without hashing the zeros.  Pack and hash (one wave
                               // per chunk): a full-length ZERO chunk gets it as its
-                              // CRC and is neither hashed nor stored
+                              // CRC and is not hashed (nor, up to 4 KiB, stored)
     uint32_t pad0;
     uint8_t *bad;             // per chunk, set to 1 when verification fails
     DevPlan *plan_rw;         // bad_count lives here

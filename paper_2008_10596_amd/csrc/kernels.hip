@@ -799,7 +799,7 @@ struct TileOut {
 };
 
 // Pack / hash of a full-length ZERO chunk: its CRC is that of C zero bytes,
-// known beforehand, and the dense image leaves it unwritten.
+// known beforehand.
 __device__ __forceinline__ void record_zero_chunk(const ChunkArgs &a, const TileOut &out, int slot, const Desc &d)
 {
     uint8_t f = kFlagZero;
@@ -866,13 +866,11 @@ __device__ __forceinline__ void small_chunk(const ChunkArgs &a, const Tabs &T, c
 // The wave goes through its chunks batch by batch (kLoadsInFlight rounds), in
 // the window of wave_rounds, with the next batch's loads (of this chunk or of
 // the wave's next) in flight while it hashes and stores the current one.
-// Bound by HBM, so ZERO memory is read only: until a chunk's first non-zero
-// batch nothing is stored or hashed.  If one comes, the zeros before it are
-// stored then, and their part of the register is the complemented init moved
-// over them.  A full-length ZERO chunk has a known CRC, and the dense image
-// leaves ZERO chunks unwritten.  (4 GiB in chunks of 64 KiB, half of the
-// allocations zero: the snapshot took 1.66 ms with every byte stored and
-// hashed.)
+// Bound by HBM.  Every byte of a pack is stored (unlike in the small form, a
+// ZERO chunk's too: callers find zeros there), but until a chunk's first
+// non-zero batch nothing is hashed.  If one comes, the zeros' part of the
+// register is the complemented init moved over them.  A full-length ZERO chunk
+// has a known CRC.
 
 // One chunk as the wave sees it: uniform over the wave.
 struct LongItem {
@@ -993,6 +991,21 @@ __device__ __forceinline__ void long_batch(const ChunkArgs &a, const Tabs &T, co
         return;
     }
     long_cut<MODE>(x, lane, r_win, rb, v);
+    if (MODE != kModeHash) {
+        if (long_full(x, r_win, rb) && !(MODE == kModeRestore && last && (x.len & 15) != 0)) {
+            uint8_t *q = (uint8_t *)x.dst + (uint32_t)long_piece(x, lane, rb) * 16;
+#pragma unroll
+            for (int b = 0; b < B; b++)
+                st16<NT>(q + b * kRoundBytes, v[b]);
+        } else {
+#pragma unroll
+            for (int b = 0; b < B; b++) {
+                const int p = long_piece(x, lane, rb + b);
+                if (rb + b < r_win && p >= 0)
+                    long_store<MODE, NT>(x, p, v[b]);
+            }
+        }
+    }
     if (MODE != kModeRestore && !*seen) {
         uint32_t o = 0;
 #pragma unroll
@@ -1014,33 +1027,11 @@ __device__ __forceinline__ void long_batch(const ChunkArgs &a, const Tabs &T, co
             return;
         }
         *seen = true;
-        if (rb > x.r0) {
-            if (MODE == kModePack)
-                for (uint32_t r = x.r0; r < rb; r++) {
-                    const int p = (int)(r * kPerRound + lane) - (int)x.z;
-                    if (p >= 0)
-                        long_store<MODE, NT>(x, p, make_uint4(0u, 0u, 0u, 0u));
-                }
+        if (rb > x.r0)
             *acc = long_zero_prefix(T, x, lane, rb);
-        }
     }
     uint32_t c[B];
     uint32_t s = *acc;
-    if (MODE != kModeHash) {
-        if (long_full(x, r_win, rb) && !(MODE == kModeRestore && last && (x.len & 15) != 0)) {
-            uint8_t *q = (uint8_t *)x.dst + (uint32_t)long_piece(x, lane, rb) * 16;
-#pragma unroll
-            for (int b = 0; b < B; b++)
-                st16<NT>(q + b * kRoundBytes, v[b]);
-        } else {
-#pragma unroll
-            for (int b = 0; b < B; b++) {
-                const int p = long_piece(x, lane, rb + b);
-                if (rb + b < r_win && p >= 0)
-                    long_store<MODE, NT>(x, p, v[b]);
-            }
-        }
-    }
     if (rb == x.r0 && long_piece(x, lane, rb) == 0)   // the first data piece carries the complemented init
         v[0].x ^= init_mask(x.len);
     chain_pieces<B>(T, v, c);

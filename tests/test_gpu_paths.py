@@ -407,3 +407,35 @@ def test_small_drains_keep_little_more_than_they_hold(filled):
     check_restored(dsts, tensors)
     img.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("C, waves", [(4112, 1), (8192, 1), (65536, 1), (262144, 1), (65536, 4)])
+@pytest.mark.parametrize("rows", [6, 70])
+def test_packs_above_4_KiB_store_zero_chunks(C, waves, rows):
+    """Chunks above 4 KiB are stored whatever they hold: a dense buffer that
+    held other bytes (the caller's, or the context's staging) has zeros where
+    the memory has, and the whole dense image is the oracle's."""
+    sizes = [2 * C, C + 33, 3 * C - 5, 1, C - 16, 2 * C + 1024] + [k % 5 * C + 7 * k + 1 for k in range(rows - 6)]
+    tensors = random_allocs(sizes, seed=92, zero=(0, 1, 3))
+    tensors[2][C:] = 0
+    ref = O.checkpoint([host(t) for t in tensors], C)
+    assert (ref["flags"] & 1).any()
+    ctx = K.Context(chunk_bytes=C, waves_per_chunk=waves, flags=K.CKPT_NO_DRAIN)
+    register_all(ctx, tensors)
+    N, D = ctx.noalloc_sizes()
+    dense = torch.full((D,), 0x5A, dtype=torch.uint8, device="cuda")
+    crc = torch.zeros(N, dtype=torch.int32, device="cuda")
+    fl = torch.zeros(N, dtype=torch.uint8, device="cuda")
+    ctx.checkpoint_noalloc(crc, fl, dense=dense)
+    assert np.array_equal(host(crc).view(np.uint32), ref["crc"]) and np.array_equal(host(fl), ref["flags"])
+    assert np.array_equal(host(dense), ref["dense"][:D])
+    saved = [t.clone() for t in tensors]
+    for t in tensors:
+        t.fill_(0x77)
+    ctx.checkpoint().close()             # the staging holds other bytes now
+    for t, x in zip(tensors, saved):
+        t.copy_(x)
+    img = ctx.checkpoint()
+    assert np.array_equal(d2h(*img.dense_ptr), ref["dense"][:D])
+    img.close()
+    ctx.close()
