@@ -97,7 +97,10 @@ enum ckpt_status {
                                      flags and the dense device copy, and no host
                                      DATA.  Without CKPT_KEEP_DENSE the dense copy
                                      is the context's staging, valid until the
-                                     context's next checkpoint or restore.       */
+                                     context's next checkpoint or restore.  A view
+                                     of it is CKPT_E_INVAL once that memory is gone
+                                     (ckpt_destroy, or a later checkpoint for which
+                                     the staging had to grow).                   */
 #define CKPT_TIMING         0x8u  /* record HIP events around each phase;
                                      read them with ckpt_last_timing             */
 #define CKPT_DRAIN_DIRECT   0x10u /* drain by kernel stores straight into pinned
@@ -173,7 +176,8 @@ typedef struct ckpt_image_meta {
     uint64_t serial;            /* unique per image within the process              */
     uint64_t base_serial;       /* incremental: serial of the base; else 0          */
     uint64_t crc_digest;        /* FNV-1a over the CRC section's 64-bit words       */
-    uint32_t has_dense;         /* 1 when CKPT_SEC_DENSE is available               */
+    uint32_t has_dense;         /* 1 when CKPT_SEC_DENSE is available (its memory
+                                   is still there)                                  */
     uint32_t drained;           /* 1 when CKPT_SEC_DATA is valid                    */
 } ckpt_image_meta;
 

@@ -235,11 +235,24 @@ def _np_view(p, nbytes, dtype):
 
 # ---- images ---------------------------------------------------------------
 
-class Image:
-    """Owns one ckpt_image; frees it on close() / garbage collection."""
+class DeviceAddress(int):
+    """The address of device memory that an image holds or points to: keeps the
+    image while it is in use (in an array interface, say)."""
 
-    def __init__(self, handle):
+    def __new__(cls, value, image):
+        self = super().__new__(cls, value)
+        self._image = image
+        return self
+
+
+class Image:
+    """Owns one ckpt_image; frees it on close() / garbage collection.  owner:
+    the context in whose staging the dense image lies (CKPT_NO_DRAIN), which
+    stays open with the image."""
+
+    def __init__(self, handle, owner=None):
         self.handle = handle
+        self._owner = owner
 
     def close(self):
         if self.handle:
@@ -293,7 +306,11 @@ class Image:
 
     @property
     def dense_ptr(self):
-        return self.view(CKPT_SEC_DENSE)
+        """(device address, bytes).  The address keeps the image and its context;
+        with a context that was closed, or whose staging has been replaced by a
+        larger one, the image's dense copy is gone and this raises."""
+        p, n = self.view(CKPT_SEC_DENSE)
+        return DeviceAddress(p, self), n
 
     def serialize(self):
         need = ctypes.c_size_t()
@@ -339,6 +356,10 @@ class Context:
         _check(lib().ckpt_init(ctypes.byref(cfg), ctypes.byref(h)), "ckpt_init")
         self.handle = h.value
         self.chunk_bytes = chunk_bytes or 4096
+        self.flags = flags
+
+    def _image(self, handle):
+        return Image(handle, self if self.flags & CKPT_NO_DRAIN else None)
 
     def close(self):
         if self.handle:
@@ -376,7 +397,7 @@ class Context:
         out = _vp()
         _check(lib().ckpt_checkpoint(self.handle, _stream_handle(stream), mode,
                                      base.handle if base else None, ctypes.byref(out)), "ckpt_checkpoint")
-        return Image(out.value)
+        return self._image(out.value)
 
     def noalloc_sizes(self):
         """(N, data_bytes) of the live set, from ckpt_checkpoint_noalloc with
@@ -505,7 +526,7 @@ def checkpoint_batch(ctxs, stream=None):
     hs = (_vp * n)(*[c.handle for c in ctxs])
     outs = (_vp * n)()
     _check(lib().ckpt_checkpoint_batch(hs, n, _stream_handle(stream), outs), "ckpt_checkpoint_batch")
-    return [Image(outs[i]) for i in range(n)]
+    return [ctxs[0]._image(outs[i]) for i in range(n)]
 
 
 # ---- serving -----------------------------------------------------------------

@@ -37,6 +37,12 @@ struct DevBuf {
     size_t cap = 0;
     int ensure(size_t bytes);
     void release();
+    // For what points into the block without owning it: true until the block
+    // at p is freed (replaced by a larger one, or with the context).
+    std::shared_ptr<const std::atomic<bool>> life();
+
+private:
+    std::shared_ptr<std::atomic<bool>> life_;   // made when first asked for
 };
 
 // Pinned host buffer from the process-wide pool; returned to the pool when
@@ -258,6 +264,8 @@ struct ckpt_image {
     ckpt::PinnedBuf ids_buf, data;
     void *dense = nullptr;
     bool dense_owned = false;
+    std::shared_ptr<const std::atomic<bool>> dense_life;   // of the context's staging, when dense points there
+    bool has_dense() const { return dense && (!dense_life || dense_life->load()); }
     ~ckpt_image();
 };
 

@@ -80,8 +80,18 @@ int DevBuf::ensure(size_t bytes)
     return CKPT_OK;
 }
 
+std::shared_ptr<const std::atomic<bool>> DevBuf::life()
+{
+    if (!life_)
+        life_ = std::make_shared<std::atomic<bool>>(p != nullptr);
+    return life_;
+}
+
 void DevBuf::release()
 {
+    if (life_)
+        life_->store(false);
+    life_.reset();
     if (p)
         (void)hipFree(p);
     p = nullptr;
@@ -1519,6 +1529,7 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
         } else if (no_drain) {
             // the context's staging: valid until its next checkpoint
             img->dense = dense + L.off[part_row[i]];
+            img->dense_life = ctx->d_dense.life();
         }
         outs[i] = img;
     }
@@ -2027,7 +2038,7 @@ extern "C" int ckpt_image_info(const ckpt_image *img, ckpt_image_meta *out)
     out->serial = img->serial;
     out->base_serial = img->base_serial;
     out->crc_digest = crc_digest(img->crc, img->N * 4);
-    out->has_dense = img->dense != nullptr;
+    out->has_dense = img->has_dense();
     out->drained = img->drained;
     return CKPT_OK;
 }
@@ -2058,6 +2069,12 @@ extern "C" int ckpt_image_view(const ckpt_image *img, int section, const void **
         *bytes = img->n_dirty * 8;
         break;
     case CKPT_SEC_DENSE:
+        if (img->dense && !img->has_dense()) {
+            *p = nullptr;
+            *bytes = 0;
+            return set_error(CKPT_E_INVAL, "the staging that held the dense image is gone: its context was destroyed, "
+                                           "or has replaced it by a larger one");
+        }
         *p = img->dense;
         *bytes = img->dense ? img->data_bytes : 0;
         break;

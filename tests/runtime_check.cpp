@@ -1,0 +1,220 @@
+// runtime_check.cpp -- drives the host runtime (csrc/runtime.cpp and
+// csrc/noalloc.cpp) on the CPU, over a stand-in for the HIP runtime: device
+// memory is host memory, streams run at once, and the kernels' launches are
+// recorded and do nothing (a selection reports the totals set here).  So it
+// shows what the host code allocates, captures, launches and refuses.
+//   runtime_check dense     a DENSE view whose staging is gone is refused
+// Exit status 0 when every check holds; the first failing check is printed.
+#include <cstdarg>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "ckpt.h"
+#include "ckpt_runtime.h"
+
+using namespace ckpt;
+
+#define CHECK(cond)                                                                  \
+    do {                                                                             \
+        if (!(cond)) {                                                               \
+            printf("line %d: %s (%s)\n", __LINE__, #cond, ckpt_last_error());        \
+            exit(1);                                                                 \
+        }                                                                            \
+    } while (0)
+
+// ------------------------------------------------- stand-in for HIP runtime
+
+namespace {
+int g_captures = 0;          // graphs instantiated
+uint64_t g_sel_bytes = 0, g_sel_count = 0;
+struct Launch {
+    std::string what;
+    int grid;
+};
+std::vector<Launch> g_launches;
+int handle;                  // streams, events and graphs are its address
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n) { *p = calloc(1, (n + 255) & ~size_t(255)); return hipSuccess; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+hipError_t hipHostFree(void *p) { return hipFree(p); }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int)
+{
+    *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 0;
+    return hipSuccess;
+}
+const char *hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)&handle; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)&handle; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { *g = (hipGraph_t)&handle; return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, char *, size_t)
+{
+    g_captures++;
+    *x = (hipGraphExec_t)&handle;
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+hipError_t hipMemPrefetchAsync(const void *, size_t, int, hipStream_t) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
+}
+
+namespace ckpt {
+hipError_t launch_prologue(hipStream_t, const PrologueArgs &a, uint64_t)
+{
+    *a.plan = *a.up_plan;
+    return hipSuccess;
+}
+hipError_t launch_prologue_small(hipStream_t, const PrologueArgs &, const SmallTable &)
+{
+    g_launches.push_back({"prologue_small", 1});
+    return hipSuccess;
+}
+hipError_t launch_chunks(hipStream_t, int mode, const ChunkArgs &, int grid, int)
+{
+    g_launches.push_back({mode == kModeRestore ? "restore" : mode == kModePack ? "pack" : "hash", grid});
+    return hipSuccess;
+}
+hipError_t launch_chunks_table(hipStream_t, int, const ChunkArgs &, const SmallTable &, int grid, int)
+{
+    g_launches.push_back({"chunks_table", grid});
+    return hipSuccess;
+}
+bool table_fits(uint64_t n, uint64_t N, int grid) { return n && n <= kRowTile && N <= (uint64_t)grid * 32; }
+hipError_t launch_select(hipStream_t, const SelArgs &a, uint64_t, bool)
+{
+    if (a.h_plan) {
+        a.h_plan->sel_bytes = g_sel_bytes;
+        a.h_plan->sel_count = g_sel_count;
+    }
+    return hipSuccess;
+}
+hipError_t launch_gather(hipStream_t, const GatherArgs &a, int grid)
+{
+    g_launches.push_back({a.out_host ? "gather_host" : "gather", grid});
+    return hipSuccess;
+}
+hipError_t launch_pick_u64(hipStream_t, const uint64_t *, const uint64_t *, uint64_t *, uint32_t) { return hipSuccess; }
+hipError_t launch_table_split(hipStream_t, const uint64_t *, uint64_t, DevPlan *, uint64_t *, uint64_t *)
+{
+    g_launches.push_back({"table_split", 1});
+    return hipSuccess;
+}
+hipError_t launch_layout_scan(hipStream_t, DevPlan *, const uint64_t *, uint32_t, uint64_t *, uint64_t *) { return hipSuccess; }
+hipError_t launch_chunk_map(hipStream_t, const DevPlan *, const uint64_t *, uint32_t *, int) { return hipSuccess; }
+// parts of the library that these checks do not enter
+std::recursive_mutex &hook_mutex() { static std::recursive_mutex m; return m; }
+void hook_forget(ckpt_ctx *) {}
+void vmm_release_all(ckpt_ctx *) {}
+}  // namespace ckpt
+
+// -------------------------------------------------------------------- checks
+
+namespace {
+
+ckpt_ctx *context(uint32_t flags, uint32_t C = 4096)
+{
+    ckpt_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.flags = flags;
+    cfg.chunk_bytes = C;
+    ckpt_ctx *ctx = nullptr;
+    CHECK(ckpt_init(&cfg, &ctx) == CKPT_OK);
+    return ctx;
+}
+
+// Nothing reads registered memory here.
+void log_memory(ckpt_ctx *ctx, uint64_t addr, uint64_t bytes)
+{
+    ckpt_id id;
+    CHECK(ckpt_register(ctx, (void *)addr, bytes, CKPT_DEVICE, &id) == CKPT_OK);
+}
+
+ckpt_image *checkpoint(ckpt_ctx *ctx, int mode = CKPT_FULL, const ckpt_image *base = nullptr)
+{
+    ckpt_image *img = nullptr;
+    CHECK(ckpt_checkpoint(ctx, nullptr, mode, base, &img) == CKPT_OK);
+    return img;
+}
+
+bool has_dense(const ckpt_image *img)
+{
+    const void *p = nullptr;
+    size_t n = 0;
+    ckpt_image_meta m;
+    CHECK(ckpt_image_info(img, &m) == CKPT_OK);
+    const int rc = ckpt_image_view(img, CKPT_SEC_DENSE, &p, &n);
+    CHECK(rc == CKPT_OK || (rc == CKPT_E_INVAL && !p && !n));
+    CHECK((rc == CKPT_OK) == (m.has_dense != 0));
+    return rc == CKPT_OK;
+}
+
+// A DENSE view into the context's staging is given only while that memory is there.
+void check_dense()
+{
+    for (uint32_t flags : {CKPT_NO_DRAIN, CKPT_NO_DRAIN | CKPT_GRAPH}) {
+        ckpt_ctx *ctx = context(flags);
+        log_memory(ctx, 1 << 20, 10000);
+        ckpt_image *a = checkpoint(ctx);
+        CHECK(has_dense(a));
+        ckpt_image *b = checkpoint(ctx);       // the same staging
+        CHECK(has_dense(a) && has_dense(b));
+        log_memory(ctx, 1 << 30, 64 << 20);    // the staging is replaced by a larger one
+        ckpt_image *c = checkpoint(ctx);
+        CHECK(!has_dense(a) && !has_dense(b) && has_dense(c));
+        ckpt_destroy(ctx);
+        CHECK(!has_dense(c));
+        for (ckpt_image *x : {a, b, c})
+            ckpt_image_free(x);
+    }
+    // images of a batch point into the first context's staging
+    ckpt_ctx *two[2] = {context(CKPT_NO_DRAIN), context(CKPT_NO_DRAIN)};
+    log_memory(two[0], 1 << 20, 5000);
+    log_memory(two[1], 1 << 30, 7000);
+    ckpt_image *img[2];
+    CHECK(ckpt_checkpoint_batch(two, 2, nullptr, img) == CKPT_OK);
+    ckpt_destroy(two[1]);
+    CHECK(has_dense(img[0]) && has_dense(img[1]));
+    ckpt_destroy(two[0]);
+    CHECK(!has_dense(img[0]) && !has_dense(img[1]));
+    // an image that owns its dense copy keeps it
+    ckpt_ctx *ctx = context(CKPT_KEEP_DENSE | CKPT_NO_DRAIN);
+    log_memory(ctx, 1 << 20, 10000);
+    ckpt_image *own = checkpoint(ctx);
+    ckpt_destroy(ctx);
+    CHECK(has_dense(own));
+    for (ckpt_image *x : {img[0], img[1], own})
+        ckpt_image_free(x);
+}
+
+}  // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "dense")
+        check_dense();
+    else
+        return 2;
+    printf("all checks held\n");
+    return 0;
+}
