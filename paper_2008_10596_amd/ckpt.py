@@ -224,12 +224,13 @@ def _nbytes(x):
     return x.numel() * x.element_size()
 
 
-def _np_view(p, nbytes, dtype):
-    """Zero-copy numpy view of host memory owned by the library."""
+def _np_view(p, nbytes, dtype, image):
+    """Zero-copy numpy view of an image's host memory; keeps the image."""
     dt = np.dtype(dtype)
     if not p or nbytes == 0:
         return np.zeros(0, dt)
     buf = (ctypes.c_uint8 * nbytes).from_address(p)
+    buf._image = image
     return np.frombuffer(buf, dtype=dt)
 
 
@@ -277,9 +278,9 @@ class Image:
 
     def _arr(self, section, dtype):
         p, n = self.view(section)
-        return _np_view(p, n, dtype)
+        return _np_view(p, n, dtype, self)
 
-    # numpy views (valid while the image is open)
+    # numpy views: they keep the image, and are valid until it is closed
     @property
     def allocs(self):
         return self._arr(CKPT_SEC_ALLOCS, ALLOC_DTYPE)

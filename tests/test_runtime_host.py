@@ -105,6 +105,21 @@ def test_dense_address_keeps_image_and_context(stand_in):
     assert stand_in.open == set()
 
 
+def test_host_views_keep_their_image(stand_in):
+    """A section's array, and what is made of it, keeps the image that holds
+    its memory."""
+    ctx = K.Context()
+    crc = ctx.checkpoint().crc
+    part = crc[4:8].view(np.uint8)
+    del crc
+    gc.collect()
+    assert stand_in.open == {1, 2} and part.base is not None
+    del part
+    gc.collect()
+    assert stand_in.open == {1}
+    ctx.close()
+
+
 def test_batch_images_keep_the_first_context(stand_in):
     ctxs = [K.Context(flags=K.CKPT_NO_DRAIN), K.Context(flags=K.CKPT_NO_DRAIN)]
     a, b = K.checkpoint_batch(ctxs)
