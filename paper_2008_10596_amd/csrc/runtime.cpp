@@ -1487,10 +1487,12 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
         imgs[0]->ids_buf = std::move(ids);
     }
     // This CRC array stays on the device as the base of the next increment: it
-    // changes places with the previous one (a captured graph has its address,
-    // so there it is copied).
+    // changes places with the previous one.  It is copied where the context has
+    // a captured graph, whichever call this is: the graph holds the array's
+    // address and would have to be captured again.
     const bool keep_crc = nout == 1 && N;
-    if (keep_crc && graph) {
+    const bool copy_crc = ctx->g_exec != nullptr;
+    if (keep_crc && copy_crc) {
         CKPT_TRY(ctx->d_prev_crc.ensure(N * 4));
         HIP_TRY(hipMemcpyAsync(ctx->d_prev_crc.p, ctx->d_crc.p, N * 4, hipMemcpyDeviceToDevice, s));
     }
@@ -1499,7 +1501,7 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
     if (!no_drain || incremental)
         HIP_TRY(hipStreamSynchronize(ds));
     HIP_TRY(hipStreamSynchronize(s));
-    if (keep_crc && !graph)
+    if (keep_crc && !copy_crc)
         std::swap(ctx->d_crc, ctx->d_prev_crc);
     ctx->prev_serial = keep_crc ? imgs[0]->serial : 0;
 

@@ -4,6 +4,7 @@
 // recorded and do nothing (a selection reports the totals set here).  So it
 // shows what the host code allocates, captures, launches and refuses.
 //   runtime_check dense     a DENSE view whose staging is gone is refused
+//   runtime_check graph     a captured graph is replayed while its capacities hold
 // Exit status 0 when every check holds; the first failing check is printed.
 #include <cstdarg>
 #include <cstdio>
@@ -206,6 +207,41 @@ void check_dense()
         ckpt_image_free(x);
 }
 
+// One capture, whatever other checkpoints the context takes in between.
+void check_graph()
+{
+    for (uint32_t flags : {0u, (uint32_t)CKPT_NO_DRAIN}) {
+        ckpt_ctx *ctx = context(flags | CKPT_GRAPH);
+        log_memory(ctx, 1 << 20, 1000000);
+        g_captures = 0;
+        ckpt_image *base = checkpoint(ctx);
+        for (int i = 0; i < 10; i++) {
+            for (int k = 0; k <= i % 3; k++)      // an odd and an even number of increments
+                ckpt_image_free(checkpoint(ctx, CKPT_INCREMENTAL, base));
+            ckpt_image_free(checkpoint(ctx));
+            ckpt_image_free(checkpoint(ctx, CKPT_FULL, base));   // with a base: no graph
+        }
+        CHECK(g_captures == 1);
+        ckpt_image_free(base);
+        ckpt_destroy(ctx);
+    }
+    // the first context of a batch, which also takes checkpoints of its own
+    ckpt_ctx *two[2] = {context(0), context(0)};
+    log_memory(two[0], 1 << 20, 1000000);
+    log_memory(two[1], 1 << 30, 500000);
+    g_captures = 0;
+    for (int i = 0; i < 6; i++) {
+        ckpt_image *img[2];
+        CHECK(ckpt_checkpoint_batch(two, 2, nullptr, img) == CKPT_OK);
+        ckpt_image_free(checkpoint(two[0], CKPT_INCREMENTAL, img[0]));
+        ckpt_image_free(img[0]);
+        ckpt_image_free(img[1]);
+    }
+    CHECK(g_captures == 1);
+    for (ckpt_ctx *x : {two[0], two[1]})
+        ckpt_destroy(x);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -213,6 +249,8 @@ int main(int argc, char **argv)
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "dense")
         check_dense();
+    else if (what == "graph")
+        check_graph();
     else
         return 2;
     printf("all checks held\n");

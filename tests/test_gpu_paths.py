@@ -439,3 +439,44 @@ def test_packs_above_4_KiB_store_zero_chunks(C, waves, rows):
     assert np.array_equal(d2h(*img.dense_ptr), ref["dense"][:D])
     img.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("drain", [True, False])
+def test_graph_replays_between_increments(drain):
+    """A context that replays its captured graph and takes increments in
+    between, against the graph's images and against increments: each equals
+    the oracle's, and so do batches led by a context with a log of its own."""
+    C = 4096
+    tensors = random_allocs([MiB + 5, 70000, 4096], seed=93, zero=(1,))
+    other = random_allocs([300000], seed=94)
+    ctx = K.Context(chunk_bytes=C, flags=K.CKPT_GRAPH | (0 if drain else K.CKPT_NO_DRAIN))
+    second = K.Context(chunk_bytes=C)
+    register_all(ctx, tensors)
+    register_all(second, other)
+    base = base_crc = None
+    for i in range(8):
+        tensors[i % 3][i:i + 40] += 1
+        ref = O.checkpoint([host(t) for t in tensors], C)
+        if i % 4 == 3:
+            img, b = K.checkpoint_batch([ctx, second])
+            assert np.array_equal(b.crc, O.checkpoint([host(t) for t in other], C)["crc"])
+            b.close()
+        else:
+            img = ctx.checkpoint()
+        assert np.array_equal(img.crc, ref["crc"]) and np.array_equal(img.flags, ref["flags"])
+        if drain:
+            assert np.array_equal(img.data, ref["serialized"])
+        if base is not None:
+            base.close()
+        base, base_crc = img, ref["crc"]
+        for k in range(i % 3 + 1):                 # an odd and an even number of increments
+            tensors[0][4096 * k + i] += 1
+            dref = O.delta([host(t) for t in tensors], C, base_crc)
+            d = ctx.checkpoint(mode=K.CKPT_INCREMENTAL, base=base)
+            assert np.array_equal(d.crc, dref["crc"]) and np.array_equal(d.dirty_ids, dref["dirty_ids"])
+            if drain:
+                assert np.array_equal(d.data, dref["delta"])
+            base.close()
+            base, base_crc = d, dref["crc"]
+    for x in (base, ctx, second):
+        x.close()
