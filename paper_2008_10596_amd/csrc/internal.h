@@ -75,6 +75,7 @@ struct DevPlan {
 constexpr int kRowTile = 64;
 constexpr uint64_t kBigRow = 4096;
 constexpr uint64_t kMapPiece = 16384;
+static_assert(kMapPiece >= 2 * kBigRow, "N chunks have at most N / kBigRow pieces");
 
 struct MapPiece {
     uint64_t row, begin, end;   // chunks [begin, end) of that row

@@ -863,7 +863,7 @@ int ckpt::graph_prologue(ckpt_ctx *ctx, hipStream_t s, const std::vector<Row> &r
                          const std::vector<uint64_t> &cb, const GraphDrain *drain, bool nontemporal,
                          uint32_t *h_crc, uint8_t *h_flags)
 {
-    const uint64_t n = rows.size(), N = cb[n], data_bytes = off[n], np = map_pieces(cb);
+    const uint64_t n = rows.size(), N = cb[n], data_bytes = off[n];
     const size_t nout = drain ? drain->nout : 0;
     auto buffers = [&]() {
         std::vector<void *> v = {ctx->d_plan.p, ctx->d_addr.p, ctx->d_size.p, ctx->d_off.p, ctx->d_cb.p,
@@ -873,7 +873,7 @@ int ckpt::graph_prologue(ckpt_ctx *ctx, hipStream_t s, const std::vector<Row> &r
                 v.push_back(p);
         return v;
     };
-    const bool fits = ctx->g_exec && n <= ctx->g_n && N <= ctx->g_N && data_bytes <= ctx->g_D && np <= ctx->g_pieces &&
+    const bool fits = ctx->g_exec && n <= ctx->g_n && N <= ctx->g_N && data_bytes <= ctx->g_D &&
                       (drain != nullptr) == ctx->g_drain && nout <= ctx->g_outs && buffers() == ctx->g_ptrs &&
                       nontemporal == ctx->g_nt;
     if (!fits) {
@@ -881,7 +881,11 @@ int ckpt::graph_prologue(ckpt_ctx *ctx, hipStream_t s, const std::vector<Row> &r
             (void)hipGraphExecDestroy(ctx->g_exec);
             ctx->g_exec = nullptr;
         }
-        const uint64_t nc = grow(n, 64), Nc = grow(N, 1024), oc = drain ? grow(nout, 8) : 0, pc = grow(np, 64);
+        const uint64_t nc = grow(n, 64), Nc = grow(N, 1024), oc = drain ? grow(nout, 8) : 0;
+        // the most map pieces that Nc chunks can have (map_pieces: one for every
+        // kBigRow chunks at most), so that no table with room for its chunks is
+        // captured again for its long rows
+        const uint64_t pc = Nc / kBigRow;
         // a reserved dense block is kept (a larger image is refused by the budget)
         const uint64_t Dc = ctx->reserved ? std::max<uint64_t>(data_bytes, ctx->d_dense.cap) : grow(data_bytes, 1 << 20);
         // the drain tables: out_addr[oc], out_chunk0[oc], row_out[nc] (u32)

@@ -238,7 +238,24 @@ void check_graph()
         ckpt_image_free(img[1]);
     }
     CHECK(g_captures == 1);
-    for (ckpt_ctx *x : {two[0], two[1]})
+    // many short rows, then as many chunks in few long rows, which are mapped
+    // in pieces
+    ckpt_ctx *lead = context(CKPT_NO_DRAIN, 16), *rows = context(0, 16), *lengths = context(0, 16);
+    for (uint64_t k = 0; k < 10000; k++)
+        log_memory(rows, (1 << 20) + 512 * k, 512);
+    for (uint64_t k = 0; k < 70; k++)
+        log_memory(lengths, (1 << 30) + 65664 * k, 65664);   // 4104 chunks
+    g_captures = 0;
+    for (int i = 0; i < 4; i++)
+        for (ckpt_ctx *x : {rows, lengths}) {
+            ckpt_ctx *pair[2] = {lead, x};
+            ckpt_image *img[2];
+            CHECK(ckpt_checkpoint_batch(pair, 2, nullptr, img) == CKPT_OK);
+            ckpt_image_free(img[0]);
+            ckpt_image_free(img[1]);
+        }
+    CHECK(g_captures == 1);
+    for (ckpt_ctx *x : {two[0], two[1], lead, rows, lengths})
         ckpt_destroy(x);
 }
 
