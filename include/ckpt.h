@@ -316,6 +316,10 @@ int ckpt_checkpoint(ckpt_ctx *ctx, void *stream, int mode, const ckpt_image *bas
  *   order with CKPT_STREAM_ORDERED).  The call returns once the work is
  *   enqueued on `stream`; the outputs are complete when the stream reaches
  *   that point.
+ * Captured into a graph (CKPT_STREAM_ORDERED), a replay reads the addresses
+ *   and sizes from the context's log as it is then.  Until the last replay the
+ *   context stays, has as many live registrations as at the capture (never
+ *   more in between), and their sizes need no larger outputs.
  * Every call on one device uses that device's one array: calls whose work
  *   overlaps on one device race (the caller orders them, e.g. on one stream).
  * CKPT_E_INVAL: bad mode, CKPT_INCREMENTAL without base_crc, NULL or

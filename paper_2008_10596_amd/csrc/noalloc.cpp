@@ -132,8 +132,17 @@ extern "C" int ckpt_checkpoint_noalloc(ckpt_ctx *ctx, void *stream, int mode, co
     auto *off = (uint64_t *)(sp + kOffOff);
     auto *cb = (uint64_t *)(sp + kOffCb);
     auto *map = (uint32_t *)(sp + kOffMap);
+    // A captured pass reads the log when it is replayed, not the table and the
+    // counts of now: the log's rows may have changed by then.
+    bool captured = false;
+    if (s) {   // the null stream is not captured
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(s, &st));
+        captured = st != hipStreamCaptureStatusNone;
+    }
     SmallTable t;
-    if (n && n <= kRowTile) {
+    const bool small = n && n <= kRowTile && !captured;
+    if (small) {
         memset(&t, 0, sizeof(t));
         for (uint64_t k = 0; k < n; k++) {
             t.addr[k] = ctx->live[k].ptr;
@@ -143,14 +152,14 @@ extern "C" int ckpt_checkpoint_noalloc(ckpt_ctx *ctx, void *stream, int mode, co
         t.data_bytes = D;
     }
     // A few rows of not too many chunks go in the chunk kernel's own arguments.
-    const bool in_args = table_fits(n, N, ctx->grid_chunks);
+    const bool in_args = small && table_fits(n, N, ctx->grid_chunks);
     // Otherwise every part is rewritten before it is read: the table (n rows),
     // the plan, off/cb (scan), map (every chunk id below N).  A table of up to
     // kRowTile rows goes in a launch's arguments and one workgroup does the
     // rest (of up to 2^18 chunks: 1 MiB of map).
     if (in_args) {
         // nothing to lay out
-    } else if (n && n <= kRowTile && N <= (1u << 18)) {
+    } else if (small && N <= (1u << 18)) {
         PrologueArgs pa;
         memset(&pa, 0, sizeof(pa));
         pa.n_known = n;
@@ -190,7 +199,7 @@ extern "C" int ckpt_checkpoint_noalloc(ckpt_ctx *ctx, void *stream, int mode, co
         a.crc = crc;
         a.flags = flags;
         a.base_crc = base_crc;
-        a.n_known = N;
+        a.n_known = captured ? 0 : N;
         const int m = pack ? kModePack : kModeHash;
         if (in_args)
             HIP_TRY(launch_chunks_table(s, m, a, t, ctx->grid_chunks, cfg.block_threads));

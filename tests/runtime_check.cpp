@@ -5,6 +5,7 @@
 // shows what the host code allocates, captures, launches and refuses.
 //   runtime_check dense     a DENSE view whose staging is gone is refused
 //   runtime_check graph     a captured graph is replayed while its capacities hold
+//   runtime_check capture   what an allocation-free call puts into a capture
 // Exit status 0 when every check holds; the first failing check is printed.
 #include <cstdarg>
 #include <cstdio>
@@ -34,7 +35,10 @@ uint64_t g_sel_bytes = 0, g_sel_count = 0;
 struct Launch {
     std::string what;
     int grid;
+    uint64_t n_known = 0;
 };
+bool g_capturing = false;    // the caller's streams
+const void *g_copied = nullptr;   // source of the last copy
 std::vector<Launch> g_launches;
 int handle;                  // streams, events and graphs are its address
 }  // namespace
@@ -74,7 +78,17 @@ hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
-hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t)
+{
+    g_copied = s;
+    return hipMemcpy(d, s, n, k);
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c)
+{
+    CHECK(s);   // the null stream cannot be asked during a capture
+    *c = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipMemPrefetchAsync(const void *, size_t, int, hipStream_t) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *>(s); return hipSuccess; }
 }
@@ -90,9 +104,9 @@ hipError_t launch_prologue_small(hipStream_t, const PrologueArgs &, const SmallT
     g_launches.push_back({"prologue_small", 1});
     return hipSuccess;
 }
-hipError_t launch_chunks(hipStream_t, int mode, const ChunkArgs &, int grid, int)
+hipError_t launch_chunks(hipStream_t, int mode, const ChunkArgs &a, int grid, int)
 {
-    g_launches.push_back({mode == kModeRestore ? "restore" : mode == kModePack ? "pack" : "hash", grid});
+    g_launches.push_back({mode == kModeRestore ? "restore" : mode == kModePack ? "pack" : "hash", grid, a.n_known});
     return hipSuccess;
 }
 hipError_t launch_chunks_table(hipStream_t, int, const ChunkArgs &, const SmallTable &, int grid, int)
@@ -259,6 +273,47 @@ void check_graph()
         ckpt_destroy(x);
 }
 
+bool launched(const char *what)
+{
+    for (const Launch &l : g_launches)
+        if (l.what == what)
+            return true;
+    return false;
+}
+
+// Outside a capture the host's table and counts go with the launches; a
+// captured pass takes both from the log when it is replayed.
+void check_capture()
+{
+    static uint8_t out[1 << 22] __attribute__((aligned(256)));
+    for (uint64_t n : {5, 64, 65}) {
+        ckpt_ctx *ctx = context(CKPT_STREAM_ORDERED);
+        for (uint64_t k = 0; k < n; k++)
+            log_memory(ctx, (1 << 30) + 65536 * k, 10000 + k);
+        for (int mode : {CKPT_FULL, CKPT_INCREMENTAL})
+            for (bool capturing : {false, true}) {
+                g_capturing = capturing;
+                g_launches.clear();
+                g_copied = nullptr;
+                uint64_t N = 0;
+                CHECK(ckpt_checkpoint_noalloc(ctx, (void *)&handle, mode, (uint32_t *)out, out, sizeof(out),
+                                              (uint32_t *)out, out, 4096, &N, nullptr) == CKPT_OK);
+                CHECK(N == 3 * n);
+                if (capturing || n > 64) {
+                    CHECK(launched("table_split") && !launched("chunks_table") && !launched("prologue_small"));
+                    CHECK(g_copied == ctx->live.data());
+                    CHECK(g_launches.back().n_known == (capturing ? 0 : N));
+                } else {
+                    CHECK(launched("chunks_table") && !g_copied);
+                }
+            }
+        g_capturing = false;
+        CHECK(ckpt_checkpoint_noalloc(ctx, nullptr, CKPT_FULL, nullptr, out, sizeof(out), (uint32_t *)out, out, 4096,
+                                      nullptr, nullptr) == CKPT_OK);
+        ckpt_destroy(ctx);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -268,6 +323,8 @@ int main(int argc, char **argv)
         check_dense();
     else if (what == "graph")
         check_graph();
+    else if (what == "capture")
+        check_capture();
     else
         return 2;
     printf("all checks held\n");

@@ -480,3 +480,45 @@ def test_graph_replays_between_increments(drain):
             base, base_crc = d, dref["crc"]
     for x in (base, ctx, second):
         x.close()
+
+
+@pytest.mark.parametrize("rows", [3, 64, 65])
+def test_captured_noalloc_pass_reads_the_log_at_replay(rows):
+    """An allocation-free pass captured into a graph, replayed with eager work
+    between: after an allocation was exchanged for another (of the same size,
+    then of a smaller one), the replay covers the one that is live then."""
+    C = 4096
+    sizes = [5 * C + 17 * k + 1 for k in range(rows)]
+    tensors = random_allocs(sizes, seed=95, zero=(1,))
+    ctx = K.Context(chunk_bytes=C, flags=K.CKPT_STREAM_ORDERED)
+    register_all(ctx, tensors)
+    N, D = ctx.noalloc_sizes()
+    dense = torch.zeros(D, dtype=torch.uint8, device="cuda")
+    crc = torch.zeros(N, dtype=torch.int32, device="cuda")
+    fl = torch.zeros(N, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.checkpoint_noalloc(crc, fl, dense=dense, stream=torch.cuda.current_stream())
+    kept = []
+    for i, size in enumerate([None, sizes[0], sizes[0], 2 * C + 5, None]):
+        if size:
+            kept.append(tensors.pop(0))      # its memory stays: a stale table would read it
+            ctx.unregister(kept[-1])
+            tensors.append(random_allocs([size], seed=96 + i)[0])
+            ctx.register(tensors[-1])
+        tensors[-1][3 + i:40] += 1
+        for x in (dense, crc, fl):
+            x.fill_(0x11)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = O.checkpoint([host(t) for t in tensors], C)
+        n = ref["n_chunks"]
+        assert n <= N
+        assert np.array_equal(host(crc).view(np.uint32)[:n], ref["crc"]) and np.array_equal(host(fl)[:n], ref["flags"])
+        now = [t.numel() for t in tensors]
+        bytes_ = sum(-(-s // 16) * 16 for s in now)
+        assert_dense(host(dense)[:bytes_], ref["dense"][:bytes_], now, C, ref["flags"])
+    del graph
+    ctx.close()

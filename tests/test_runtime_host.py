@@ -25,13 +25,13 @@ def runtime_check(tmp_path_factory):
     sources = [os.path.join(ROOT, "tests", "runtime_check.cpp")]
     sources += [os.path.join(CSRC, f) for f in ("runtime.cpp", "noalloc.cpp", "crc_tables.cpp")]
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-D__HIP_PLATFORM_AMD__",
-                    "-D__align__(x)=__attribute__((aligned(x)))", "-DHIP_SYMBOL(x)=(&(x))",
+                    "-D__align__(x)=__attribute__((aligned(x)))", "-DHIP_SYMBOL(x)=((const void*)&(x))",
                     "-I", HIP, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *sources,
                     "-o", exe, "-lpthread"], check=True)
     return exe
 
 
-@pytest.mark.parametrize("what", ["dense", "graph"])
+@pytest.mark.parametrize("what", ["dense", "graph", "capture"])
 def test_host_runtime(runtime_check, what):
     r = subprocess.run([runtime_check, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "all checks held" in r.stdout, r.stdout + r.stderr
