@@ -1611,8 +1611,25 @@ extern "C" int ckpt_restore(ckpt_ctx *ctx, void *stream, const ckpt_image *img, 
 }
 
 namespace {
-// Workgroups of a scatter that reads host memory.
+// Workgroups of a scatter that reads host memory, of `items` chunks that span
+// `bytes` of memory and `ser` of the link: a few keep the link full and leave
+// it to itself (16 MiB in chunks of 4 KiB: 358 us with 64, 380 - 410 with one
+// per CU), as long as they hold enough loads in flight -- a chunk ahead per
+// wave, at most 4 KiB of it: 64 MiB in chunks of 16 / 64 / 256 / 512 bytes take
+// 11.7 / 2.96 / 1.26 / 1.24 ms with 64 and 3.25 / 1.37 / 1.25 / 1.24 with 256 --
+// and the stores are not what bounds it: an increment that zeroes 4 GiB takes
+// 1.89 ms with 64 and 1.22 with 256, 256 MiB of which 10% are not ZERO 615 and
+// 577 us, 50% 2460 and 2475.
 constexpr int kHostScatterGrid = 64;
+constexpr uint64_t kHostScatterAhead = uint64_t(512) << 10;
+
+int host_scatter_grid(const ckpt_ctx *ctx, uint64_t items, uint64_t bytes, uint64_t ser)
+{
+    const uint64_t waves = (uint64_t)kHostScatterGrid * (ctx->cfg.block_threads / 64);
+    const uint64_t ahead = std::min<uint64_t>(bytes / std::max<uint64_t>(items, 1) / ctx->cfg.waves_per_chunk, 4096);
+    const bool link_bound = ahead * waves >= kHostScatterAhead && ser >= bytes / 2;
+    return link_bound ? std::min(ctx->grid_chunks, kHostScatterGrid) : ctx->grid_chunks;
+}
 
 // The flags of the image (1) or the increment (2) select other than its serialized bytes.
 int bad_selection(uint64_t which, uint64_t found, const ckpt_image *img, const ckpt_image *delta)
@@ -1762,8 +1779,6 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
     a.want_flags = (const uint8_t *)ctx->d_flags.p;
     a.zero_crc = ctx->zero_crc;
     a.bad = (uint8_t *)ctx->d_bad.p;
-    // Few workgroups saturate the link (a scatter from host memory).
-    const int direct_grid = std::min(ctx->grid_chunks, kHostScatterGrid);
     DevPlan P;
     // The flags decide which chunks are read from the serialized bytes: they
     // must account for exactly these, or a scatter would read past them.  The
@@ -1777,7 +1792,8 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
         if (timing)
             HIP_TRY(hipEventRecord(ctx->ev[1], s));
         a.n_known = N;
-        HIP_TRY(launch_chunks(s, kModeRestore, a, base_direct ? direct_grid : ctx->grid_chunks,
+        HIP_TRY(launch_chunks(s, kModeRestore, a,
+                              base_direct ? host_scatter_grid(ctx, N, img->data_bytes, img->ser_bytes) : ctx->grid_chunks,
                               ctx->cfg.block_threads));
     } else if (N) {
         CKPT_TRY(read_selection(ctx, s, &P));
@@ -1844,7 +1860,9 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
         b.want_flags = (const uint8_t *)ctx->d_flags2.p;
         b.ids = (const uint64_t *)ctx->d_ids.p;
         b.n_known = nd;
-        HIP_TRY(launch_chunks(s, kModeRestore, b, delta_direct ? direct_grid : ctx->grid_chunks,
+        const uint64_t spanned = std::min<uint64_t>(nd * img->C, img->data_bytes);   // at most, by the dirty chunks
+        HIP_TRY(launch_chunks(s, kModeRestore, b,
+                              delta_direct ? host_scatter_grid(ctx, nd, spanned, delta->ser_bytes) : ctx->grid_chunks,
                               ctx->cfg.block_threads));
     }
     if (timing)

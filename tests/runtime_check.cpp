@@ -5,6 +5,7 @@
 // shows what the host code allocates, captures, launches and refuses.
 //   runtime_check dense     a DENSE view whose staging is gone is refused
 //   runtime_check graph     a captured graph is replayed while its capacities hold
+//   runtime_check grids     workgroups of a refill from host memory
 //   runtime_check capture   what an allocation-free call puts into a capture
 // Exit status 0 when every check holds; the first failing check is printed.
 #include <cstdarg>
@@ -314,6 +315,73 @@ void check_capture()
     }
 }
 
+// The grid of a refill of one image of n allocations of `bytes` each, of which
+// `ser` bytes are serialized.
+int refill_grid(uint32_t C, uint32_t block, uint32_t waves, uint64_t n, uint64_t bytes, uint64_t ser)
+{
+    ckpt_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.chunk_bytes = C;
+    cfg.block_threads = block;
+    cfg.waves_per_chunk = waves;
+    ckpt_ctx *ctx = nullptr;
+    CHECK(ckpt_init(&cfg, &ctx) == CKPT_OK);
+    std::vector<void *> dst(n);
+    for (uint64_t k = 0; k < n; k++) {
+        dst[k] = (void *)((uint64_t(1) << 32) + (bytes + 4096) / 4096 * 4096 * k);
+        log_memory(ctx, (uint64_t)dst[k], bytes);
+    }
+    g_sel_bytes = ser;
+    ckpt_image *img = checkpoint(ctx);
+    g_launches.clear();
+    CHECK(ckpt_restore(ctx, nullptr, img, nullptr, dst.data(), nullptr, n, nullptr) == CKPT_OK);
+    g_sel_bytes = 0;
+    CHECK(g_launches.size() == 1 && g_launches[0].what == "restore");
+    const int grid = g_launches[0].grid;
+    ckpt_image_free(img);
+    ckpt_destroy(ctx);
+    return grid;
+}
+
+// Few workgroups where the link bounds a refill, one per CU (256) otherwise.
+void check_grids()
+{
+    const uint64_t M = 1 << 20;
+    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 64 * M) == 64);
+    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 32 * M) == 64);
+    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 32 * M - 16) == 256);   // stores bound it
+    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 0) == 256);
+    CHECK(refill_grid(512, 0, 0, 1, 64 * M, 64 * M) == 64);
+    CHECK(refill_grid(496, 0, 0, 1, 64 * M, 64 * M) == 256);         // too few bytes in flight
+    CHECK(refill_grid(16, 0, 0, 1, 64 * M, 64 * M) == 256);
+    CHECK(refill_grid(4096, 64, 0, 1, 64 * M, 64 * M) == 256);
+    CHECK(refill_grid(4096, 256, 0, 1, 64 * M, 64 * M) == 64);
+    CHECK(refill_grid(4096, 0, 16, 1, 64 * M, 64 * M) == 256);
+    CHECK(refill_grid(65536, 0, 0, 1000, 100, 112000) == 256);       // short chunks whatever C is
+    CHECK(refill_grid(65536, 0, 0, 1000, 1000, 1008000) == 64);
+    // an increment that zeroes memory
+    ckpt_ctx *ctx = context(0);
+    log_memory(ctx, 1 << 20, 64 * M);
+    g_sel_bytes = 64 * M;
+    ckpt_image *base = checkpoint(ctx);
+    for (uint64_t ser : {uint64_t(0), M, 16 * M}) {
+        g_sel_bytes = ser;
+        g_sel_count = 4096;
+        ckpt_image *delta = checkpoint(ctx, CKPT_INCREMENTAL, base);
+        for (uint64_t i = 0; i < 4096; i++)   // no kernel has written the ids
+            ((uint64_t *)delta->ids_buf.p)[i] = i;
+        void *dst = (void *)(1 << 20);
+        g_launches.clear();
+        CHECK(ckpt_restore(ctx, nullptr, base, delta, &dst, nullptr, 1, nullptr) == CKPT_OK);
+        CHECK(g_launches.size() == 2 && g_launches[0].grid == 64);
+        CHECK(g_launches[1].grid == (ser == 16 * M ? 64 : 256));
+        ckpt_image_free(delta);
+    }
+    g_sel_bytes = g_sel_count = 0;
+    ckpt_image_free(base);
+    ckpt_destroy(ctx);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -323,6 +391,8 @@ int main(int argc, char **argv)
         check_dense();
     else if (what == "graph")
         check_graph();
+    else if (what == "grids")
+        check_grids();
     else if (what == "capture")
         check_capture();
     else
