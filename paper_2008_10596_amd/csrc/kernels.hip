@@ -2031,7 +2031,9 @@ __global__ __launch_bounds__(kSelThreads) void k_sel_down(SelArgs a)
 // The tile follows from the launch: about two per workgroup, 16 to 1024
 // chunks.  Small launches then use the whole grid: with fixed tiles of 1024
 // chunks (64 per wave, each wave copying its own chunks whole), 9 MB in 2350
-// chunks ran on 3 workgroups.
+// chunks ran on 3 workgroups.  The list's pieces are counted by the chunks' own
+// lengths: with as many units for each as a full chunk has, an increment of 300
+// allocations of 1000 bytes took 10.4 ms with chunks of 256 MiB, now 82 us.
 
 constexpr int kGatherLoads = 4;
 constexpr uint32_t kGatherPiece = kGatherLoads * 1024;
@@ -2061,13 +2063,26 @@ __device__ __forceinline__ void gather_copy(const uint8_t *s, uint8_t *d, uint32
     }
 }
 
+// The chunk of a list that unit u belongs to: the last of the `cnt` (at most
+// kGatherTile) whose first unit is at most u.  By the whole wave: every 16th
+// chunk, then the 16 from there on.
+__device__ __forceinline__ uint32_t gather_chunk(const uint32_t *first, uint32_t cnt, uint32_t u, int lane)
+{
+    static_assert(kGatherTile <= 64 * 16, "two steps");
+    const uint32_t i = 16 * (uint32_t)lane;
+    const uint32_t b = 16 * (uint32_t)(__popcll(__ballot(i < cnt && first[i] <= u)) - 1);
+    const uint32_t j = b + (uint32_t)lane;
+    return b + (uint32_t)__popcll(__ballot(lane < 16 && j < cnt && first[j] <= u)) - 1;
+}
+
 template <bool NT_ST>
 __global__ __launch_bounds__(1024) void k_gather(GatherArgs a)
 {
     __shared__ uint64_t s_t[2];
     __shared__ uint64_t s_src[kGatherTile], s_dst[kGatherTile];
     __shared__ uint32_t s_len[kGatherTile];
-    __shared__ uint32_t s_cnt[16];
+    __shared__ uint32_t s_first[kGatherTile];   // units (pieces) before the chunk's
+    __shared__ uint32_t s_cnt[16], s_units[16];
     const uint64_t N = a.g_end ? a.g_end : a.plan->n_chunks;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const uint64_t total = N > a.g_begin ? N - a.g_begin : 0;
@@ -2075,7 +2090,7 @@ __global__ __launch_bounds__(1024) void k_gather(GatherArgs a)
     while (span > kGatherMinTile && (uint64_t)span * 2 * gridDim.x > total)
         span >>= 1;
     const uint64_t n_tiles = (total + span - 1) / span;
-    const uint32_t pieces = (a.C + kGatherPiece - 1) / kGatherPiece;   // of a full chunk
+    const bool one_piece = a.C <= kGatherPiece;   // then unit u is the list's chunk u
     // Workgroup b's first tile is tile b; the rest are taken in order from the
     // plan's counter by thread 0, so that a workgroup whose tiles hold few
     // selected chunks takes more of them.
@@ -2122,31 +2137,46 @@ __global__ __launch_bounds__(1024) void k_gather(GatherArgs a)
             }
         }
         const uint64_t m = __ballot(take);
-        if (lane == 0)
-            s_cnt[wave] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t pos = 0, cnt = 0;
-        for (int w = 0; w < nw; w++) {
-            if (w == wave)
-                pos = cnt;
-            cnt += s_cnt[w];
+        // units by the chunks' own lengths: a tile of short chunks has few, whatever C is
+        const uint32_t mine = one_piece ? 0 : (len + kGatherPiece - 1) / kGatherPiece;
+        uint32_t upto = mine;
+        if (!one_piece) {
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t v = __shfl_up(upto, d, 64);
+                upto += lane >= d ? v : 0;
+            }
         }
+        if (lane == 63) {
+            s_cnt[wave] = (uint32_t)__popcll(m);
+            s_units[wave] = upto;
+        }
+        __syncthreads();
+        uint32_t pos = 0, cnt = 0, first = upto - mine, units = 0;
+        for (int w = 0; w < nw; w++) {
+            if (w == wave) {
+                pos = cnt;
+                first += units;
+            }
+            cnt += s_cnt[w];
+            units += s_units[w];
+        }
+        if (one_piece)
+            units = cnt;
         if (take) {
             pos += (uint32_t)__popcll(m & ((1ull << lane) - 1));
             s_src[pos] = src;
             s_dst[pos] = dst;
             s_len[pos] = len;
+            s_first[pos] = first;
         }
         __syncthreads();
-        for (uint32_t u = wave; u < cnt * pieces; u += nw) {   // uniform over the wave
-            const uint32_t c = u / pieces;
-            const uint32_t o = (u - c * pieces) * kGatherPiece;
-            const uint32_t n = uniform_u32(s_len[c]);
-            if (o < n) {
-                const uint32_t here = n - o < kGatherPiece ? n - o : kGatherPiece;
-                gather_copy<NT_ST>((const uint8_t *)uniform_u64(s_src[c]) + o, (uint8_t *)uniform_u64(s_dst[c]) + o,
-                                   here, a.from_dense != 0, lane);
-            }
+        for (uint32_t u = wave; u < units; u += nw) {   // uniform over the wave
+            const uint32_t c = one_piece ? u : gather_chunk(s_first, cnt, u, lane);
+            const uint32_t o = one_piece ? 0 : (u - uniform_u32(s_first[c])) * kGatherPiece;
+            const uint32_t n = uniform_u32(s_len[c]) - o;
+            gather_copy<NT_ST>((const uint8_t *)uniform_u64(s_src[c]) + o, (uint8_t *)uniform_u64(s_dst[c]) + o,
+                               n < kGatherPiece ? n : kGatherPiece, a.from_dense != 0, lane);
         }
     }
 }

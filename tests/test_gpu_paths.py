@@ -1,6 +1,8 @@
 """Bit-exact parity with the oracle where a path changes form: staging of few
 segments, remainders and edges of the kernels' tiles.
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -522,3 +524,54 @@ def test_captured_noalloc_pass_reads_the_log_at_replay(rows):
         assert_dense(host(dense)[:bytes_], ref["dense"][:bytes_], now, C, ref["flags"])
     del graph
     ctx.close()
+
+
+@pytest.mark.parametrize("C, n, longest", [(8192, 1500, 8192), (1 << 20, 1500, 300000), (1 << 28, 300, 5 * MiB),
+                                           (1 << 30, 40, 3 * MiB + 7)])
+def test_gather_of_short_chunks_under_a_large_chunk_size(C, n, longest):
+    """Allocations much shorter than a chunk, a few long ones among them:
+    increments, direct drains and the server's images are the oracle's, and an
+    increment of short allocations takes as long as with 4 KiB chunks."""
+    log("%d short allocations, C=%d" % (n, C))
+    sizes = [100 + 37 * k % 900 for k in range(n)]
+    for k in (0, n // 2, n - 1):
+        sizes[k] = longest
+    sizes[n // 3] = 4097
+    tensors = random_allocs(sizes, seed=97, zero=(5,))
+    ref = O.checkpoint([host(t) for t in tensors], C)
+    ctx = K.Context(chunk_bytes=C, flags=K.CKPT_DRAIN_DIRECT)
+    register_all(ctx, tensors)
+    img = ctx.checkpoint()
+    check_full(img, ref, tensors, C)
+    for t in tensors[::2]:
+        t[-1:] += 1
+    dref = O.delta([host(t) for t in tensors], C, ref["crc"])
+    for flags in (0, K.CKPT_DRAIN_DIRECT):
+        with K.Context(chunk_bytes=C, flags=flags) as other:
+            register_all(other, tensors)
+            d = other.checkpoint(mode=K.CKPT_INCREMENTAL, base=img)
+            assert np.array_equal(d.dirty_ids, dref["dirty_ids"]) and np.array_equal(d.data, dref["delta"])
+            d.close()
+    srv = K.Server(chunk_bytes=C, staging_budget=64 * MiB)
+    res = srv.wait(srv.submit(K.CKPT_REQ_CHECKPOINT, tensors))
+    assert res["status"] == K.CKPT_OK
+    check_full(res["image"], O.checkpoint([host(t) for t in tensors], C), tensors, C)
+    for x in (res["image"], srv, img, ctx):
+        x.close()
+    short = [t for t in tensors if t.numel() < 1000]
+    best = []
+    for chunk in (4096, C):
+        with K.Context(chunk_bytes=chunk) as c:
+            register_all(c, short)
+            base = c.checkpoint()
+            for t in short:
+                t += 1
+            times = []
+            for _ in range(10):
+                t0 = time.perf_counter()
+                c.checkpoint(mode=K.CKPT_INCREMENTAL, base=base).close()
+                times.append(time.perf_counter() - t0)
+            base.close()
+            best.append(min(times))
+    log("  increment of %d short allocations: %.0f us, with 4 KiB chunks %.0f us" % (len(short), best[1] * 1e6, best[0] * 1e6))
+    assert best[1] < 5 * best[0] + 200e-6
