@@ -8,12 +8,12 @@
 // join the step loop: each step is ONE launch of the row-mode chunk kernel
 // that processes up to step_bytes of every stepping request, packing some and
 // restoring others.  A request whose chunks are all processed is finished by
-// an auxiliary worker (checkpoint: a gather, after the selection scan that its
-// last step ends with, straight to pinned host memory; restore: the
-// verification count) while later steps keep the GPU busy with the other
-// requests.  Requests that arrive meanwhile join at the next step.  Admission
-// (admission.h) counts the device staging of every request and, for a
-// checkpoint, the pinned host memory of the image it will produce.
+// an auxiliary worker (checkpoint: selection scan, gather, copy of the
+// serialized image to pinned host memory; restore: the verification count)
+// while later steps keep the GPU busy with the other requests.  Requests that
+// arrive meanwhile join at the next step.  Admission (admission.h) counts the
+// device staging of every request and, for a checkpoint, the pinned host
+// memory of the image it will produce.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -74,7 +74,6 @@ struct Req {
     const ckpt_image *image = nullptr;
     std::vector<uint64_t> off, cb;  // host layout, n + 1 each
     uint64_t N = 0, data_bytes = 0, live = 0, ser_bytes = 0;
-    uint64_t sel_bytes = 0;         // checkpoint: of the serialized image, known after its last step
     uint64_t host_charge = 0;       // checkpoint: most pinned bytes its image can take
     bool waited_host = false;       // was held back for host memory
     bool mem_waited = false;        // a step of it waited for memory
@@ -84,7 +83,7 @@ struct Req {
     uint64_t *d_addr = nullptr, *d_size = nullptr, *d_off = nullptr, *d_cb = nullptr, *d_soff = nullptr;
     uint64_t *d_tile_b = nullptr, *d_tile_c = nullptr;
     uint32_t *d_map = nullptr, *d_crc = nullptr;
-    uint8_t *d_flags = nullptr, *d_bad = nullptr, *d_dense = nullptr, *d_staging = nullptr;
+    uint8_t *d_flags = nullptr, *d_bad = nullptr, *d_dense = nullptr, *d_compact = nullptr, *d_staging = nullptr;
     DevPlan *d_plan = nullptr;
     uint64_t next_chunk = 0;
     State state = kQueued;
@@ -101,12 +100,6 @@ struct Task {
 // finish_request: the image's pinned host memory could not be allocated now
 // (the request keeps its staging and is finished again later)
 constexpr int kRetryHost = 1;
-// Workgroups of a finished checkpoint's gather, which stores to host memory: a
-// few fill the link, and several gathers and a step run side by side (a burst
-// of 9 checkpoints and 3 restores, 12 times 8 to 64 MiB: 4.75 ms with 16, 4.78
-// with 32, 4.75 with 64).  The runtime's copies from a staged gather took 4.64
-// ms in some processes and 5.53 in the others, by the engine it chose.
-constexpr int kFinishGrid = 16;
 // how long a request (or a step) may wait for memory before it fails
 constexpr double kHostWaitLimitMs = 30000.0;
 constexpr int kHostRetryMs = 2;
@@ -129,14 +122,13 @@ struct ckpt_server {
     std::vector<Req *> active;                    // admitted, not done
     std::unordered_map<uint64_t, Req *> by_ticket;
     std::deque<Task> aux_tasks;
-    uint32_t n_to_host = 0, n_to_device = 0;      // tasks under way that copy over the link, by direction
     AdmitState adm;                               // slots and host reservations
     bool host_blocked = false;                    // a checkpoint waits for host memory
     const Req *held = nullptr;                    // that checkpoint, held back since t_held
     Clock::time_point t_held{};
 
     // step buffers (owned by the step thread)
-    PinnedBuf h_step, h_sel;
+    PinnedBuf h_step;
     DevBuf d_step, d_map;
 
     std::thread step_thread;
@@ -193,9 +185,7 @@ uint64_t plan_block(Req *r, uint8_t *base)
     r->d_tile_c = (uint64_t *)take(8 * tiles);
     if (r->op == CKPT_REQ_CHECKPOINT) {
         r->d_dense = take(r->data_bytes);
-        // the serialized bytes once more: gathered straight to the host now, but
-        // what the budget admits does not depend on how they get there
-        (void)take(r->data_bytes);
+        r->d_compact = take(r->data_bytes);
     } else {
         r->d_bad = take(N);
         r->d_staging = take(r->ser_bytes);
@@ -272,15 +262,15 @@ int prep_request(ckpt_server *sv, Req *r, hipStream_t s, PinnedBuf &up)
     return CKPT_OK;
 }
 
-// Checkpoint: gather to pinned memory, build the image.
+// Checkpoint: select, gather, copy to pinned memory, build the image.
 // Restore: read the verification count.
 int finish_request(ckpt_server *sv, Req *r, hipStream_t s, PinnedBuf &up)
 {
     const uint64_t N = r->N;
     const uint32_t C = sv->cfg.chunk_bytes;
+    CKPT_TRY(up.ensure(sizeof(DevPlan)));
+    auto *plan = (DevPlan *)up.p;
     if (r->op == CKPT_REQ_RESTORE) {
-        CKPT_TRY(up.ensure(sizeof(DevPlan)));
-        auto *plan = (DevPlan *)up.p;
         REQ_HIP(r, hipMemcpyAsync(plan, r->d_plan, sizeof(DevPlan), hipMemcpyDeviceToHost, s));
         REQ_HIP(r, hipStreamSynchronize(s));
         r->result.n_bad = plan->bad_count;
@@ -319,7 +309,15 @@ int finish_request(ckpt_server *sv, Req *r, hipStream_t s, PinnedBuf &up)
         a.off = r->off[k];
         a.cb = r->cb[k];
     }
-    const uint64_t sel = r->sel_bytes;
+    uint64_t sel = 0;
+    if (N) {
+        SelArgs a = sel_args(r, kSelNonZero, r->d_flags);
+        a.C = C;
+        a.h_plan = plan;
+        REQ_HIP(r, launch_select(s, a, N, false));
+        REQ_HIP(r, hipStreamSynchronize(s));
+        sel = plan->sel_bytes;
+    }
     img->ser_bytes = sel;
     if (alloc_meta(img.get(), N) || img->data.ensure(std::max<uint64_t>(sel, 1))) {
         // nothing is queued into the image's buffers yet: give them back and
@@ -342,13 +340,11 @@ int finish_request(ckpt_server *sv, Req *r, hipStream_t s, PinnedBuf &up)
         g.dense = r->d_dense;
         g.flags = r->d_flags;
         g.soff = r->d_soff;
-        g.out = (uint8_t *)img->data.p;
-        g.out_host = 1;
-        g.copy[0] = {r->d_crc, img->crc, 4 * N};
-        g.copy[1] = {r->d_flags, img->flags, N};
-        g.n_copy = 2;
-        REQ_HIP(r, launch_gather(s, g, kFinishGrid));
-    } else if (N) {
+        g.out = r->d_compact;
+        REQ_HIP(r, launch_gather(s, g, sv->cu_count));
+        REQ_HIP(r, hipMemcpyAsync(img->data.p, r->d_compact, sel, hipMemcpyDeviceToHost, s));
+    }
+    if (N) {
         REQ_HIP(r, hipMemcpyAsync(img->crc, r->d_crc, 4 * N, hipMemcpyDeviceToHost, s));
         REQ_HIP(r, hipMemcpyAsync(img->flags, r->d_flags, N, hipMemcpyDeviceToHost, s));
     }
@@ -478,37 +474,6 @@ void admit_locked(ckpt_server *sv)
     }
 }
 
-bool copies_to_host(const Task &t) { return !t.prep && t.req->op == CKPT_REQ_CHECKPOINT; }
-bool copies_to_device(const Task &t) { return t.prep && t.req->op == CKPT_REQ_RESTORE; }
-
-// The task that runs next, of those that may run now (caller holds sv->mu):
-// the oldest of the short ones, which copy nothing over the link and on whose
-// end other threads wait; else the oldest of the direction that fewer threads
-// are copying in, since the link carries both at once.  While a checkpoint is
-// on its way, one restore at a time is copied to the device, so that a thread
-// is free to copy the checkpoint to the host.
-std::deque<Task>::iterator next_task(ckpt_server *sv, Clock::time_point now)
-{
-    auto &q = sv->aux_tasks;
-    bool coming = false;   // a checkpoint that will copy to the host soon
-    for (const Req *r : sv->active)
-        coming = coming || (r->op == CKPT_REQ_CHECKPOINT && r->state != kFinish);
-    auto best = q.end();
-    int best_rank = 3;
-    for (auto it = q.begin(); it != q.end(); ++it) {
-        if (it->not_before > now || (coming && sv->n_to_device && copies_to_device(*it)))
-            continue;
-        const int rank = copies_to_host(*it)     ? (sv->n_to_host <= sv->n_to_device ? 1 : 2)
-                         : copies_to_device(*it) ? (sv->n_to_device <= sv->n_to_host ? 1 : 2)
-                                                 : 0;
-        if (rank < best_rank) {
-            best = it;
-            best_rank = rank;
-        }
-    }
-    return best;
-}
-
 void aux_loop(ckpt_server *sv)
 {
     DeviceGuard g(sv->cfg.device);
@@ -522,24 +487,23 @@ void aux_loop(ckpt_server *sv)
             for (;;) {
                 if (sv->aux_tasks.empty() && sv->stop)
                     break;
-                // a task that may run now; else wait for the earliest
+                // the first task that may run now; else wait for the earliest
                 const auto now = Clock::now();
-                auto it = next_task(sv, now);
+                auto it = std::find_if(sv->aux_tasks.begin(), sv->aux_tasks.end(),
+                                       [&](const Task &x) { return x.not_before <= now; });
                 if (it != sv->aux_tasks.end()) {
                     t = *it;
                     sv->aux_tasks.erase(it);
-                    sv->n_to_host += copies_to_host(t);
-                    sv->n_to_device += copies_to_device(t);
                     break;
                 }
-                auto first = Clock::time_point::max();
-                for (const Task &x : sv->aux_tasks)   // the end of a copy to the device wakes what it held back
-                    if (x.not_before > now)
-                        first = std::min(first, x.not_before);
-                if (first == Clock::time_point::max())
+                if (sv->aux_tasks.empty()) {
                     sv->cv_aux.wait(lk);
-                else
+                } else {
+                    auto first = sv->aux_tasks.front().not_before;
+                    for (const Task &x : sv->aux_tasks)
+                        first = std::min(first, x.not_before);
                     sv->cv_aux.wait_until(lk, first);
+                }
             }
             if (!t.req)
                 break;   // stopping
@@ -548,14 +512,6 @@ void aux_loop(ckpt_server *sv)
         int rc = t.prep ? prep_request(sv, r, s, up) : finish_request(sv, r, s, up);
         if (rc != CKPT_OK)
             (void)hipStreamSynchronize(s);   // nothing of r may still be queued when its block is freed
-        {
-            std::lock_guard<std::mutex> lk(sv->mu);
-            sv->n_to_host -= copies_to_host(t);
-            if (copies_to_device(t)) {
-                sv->n_to_device--;
-                sv->cv_aux.notify_all();
-            }
-        }
         if (rc == kRetryHost || rc == CKPT_E_NOMEM) {
             // Memory is short right now: pinned host memory for the image
             // (kRetryHost) or for a staging buffer, or device memory.  The
@@ -733,7 +689,6 @@ int run_step(ckpt_server *sv, const std::vector<Req *> &reqs, std::vector<uint64
     CKPT_TRY(sv->h_step.ensure(bytes));
     CKPT_TRY(sv->d_step.ensure(bytes));
     CKPT_TRY(sv->d_map.ensure(items * 4));
-    CKPT_TRY(sv->h_sel.ensure(reqs.size() * sizeof(DevPlan)));
     uint8_t *h = (uint8_t *)sv->h_step.p;
     DevPlan plan;
     memset(&plan, 0, sizeof(plan));
@@ -756,23 +711,7 @@ int run_step(ckpt_server *sv, const std::vector<Req *> &reqs, std::vector<uint64
     a.map = (const uint32_t *)sv->d_map.p;
     a.tile_ctr = &((DevPlan *)d)->tile_next;
     HIP_TRY(launch_rows(s, a, sv->cu_count, sv->cfg.block_threads));
-    // Checkpoints that end with this step: what to gather.  Here and not at the
-    // finish: a select beside another worker's gather ends only with that
-    // gather (its stores to the host are under way all the time), and until
-    // the next gather starts the link is idle.
-    auto *sel = (DevPlan *)sv->h_sel.p;
-    const auto ends_here = [&](size_t i) { return reqs[i]->op == CKPT_REQ_CHECKPOINT && ends[i] >= reqs[i]->N; };
-    for (size_t i = 0; i < reqs.size(); i++)
-        if (ends_here(i)) {
-            SelArgs sa = sel_args(reqs[i], kSelNonZero, reqs[i]->d_flags);
-            sa.C = C;
-            sa.h_plan = &sel[i];
-            HIP_TRY(launch_select(s, sa, reqs[i]->N, false));
-        }
     HIP_TRY(hipStreamSynchronize(s));
-    for (size_t i = 0; i < reqs.size(); i++)
-        if (ends_here(i))
-            reqs[i]->sel_bytes = sel[i].sel_bytes;
     return CKPT_OK;
 }
 

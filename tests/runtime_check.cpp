@@ -1,17 +1,20 @@
-// runtime_check.cpp -- drives the host runtime (csrc/runtime.cpp and
-// csrc/noalloc.cpp) on the CPU, over a stand-in for the HIP runtime: device
+// runtime_check.cpp -- drives the host runtime (csrc/runtime.cpp,
+// csrc/noalloc.cpp and csrc/server.cpp) on the CPU, over a stand-in for the HIP runtime: device
 // memory is host memory, streams run at once, and the kernels' launches are
 // recorded and do nothing (a selection reports the totals set here).  So it
 // shows what the host code allocates, captures, launches and refuses.
 //   runtime_check dense     a DENSE view whose staging is gone is refused
 //   runtime_check graph     a captured graph is replayed while its capacities hold
+//   runtime_check server    restores beside a checkpoint; finishes through staging
 //   runtime_check grids     workgroups of a refill from host memory
 //   runtime_check capture   what an allocation-free call puts into a capture
 // Exit status 0 when every check holds; the first failing check is printed.
-#include <cstdarg>
+#include <chrono>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -40,7 +43,24 @@ struct Launch {
 };
 bool g_capturing = false;    // the caller's streams
 const void *g_copied = nullptr;   // source of the last copy
-std::vector<Launch> g_launches;
+struct Launches : std::vector<Launch> {
+    std::mutex mu;
+    void push_back(const Launch &l)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        std::vector<Launch>::push_back(l);
+    }
+} g_launches;
+// The server's threads meet here: copies of an image to the device, and steps,
+// wait (2 s at most) until `wanted` copies are under way at once; the first step
+// waits until it is released.
+struct Meet {
+    std::mutex mu;
+    std::condition_variable cv;
+    int copies = 0, most = 0, wanted = 0;
+    uint64_t bytes = 0;
+    bool hold_step = false, in_step = false;
+} g_meet;
 int handle;                  // streams, events and graphs are its address
 }  // namespace
 
@@ -82,6 +102,14 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t)
 {
     g_copied = s;
+    std::unique_lock<std::mutex> lk(g_meet.mu);
+    if (g_meet.wanted && k == hipMemcpyHostToDevice && n == g_meet.bytes) {
+        g_meet.most = std::max(g_meet.most, ++g_meet.copies);
+        g_meet.cv.notify_all();
+        g_meet.cv.wait_for(lk, std::chrono::seconds(2), [] { return g_meet.most >= g_meet.wanted; });
+        g_meet.copies--;
+    }
+    lk.unlock();
     return hipMemcpy(d, s, n, k);
 }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c)
@@ -137,6 +165,16 @@ hipError_t launch_table_split(hipStream_t, const uint64_t *, uint64_t, DevPlan *
 }
 hipError_t launch_layout_scan(hipStream_t, DevPlan *, const uint64_t *, uint32_t, uint64_t *, uint64_t *) { return hipSuccess; }
 hipError_t launch_chunk_map(hipStream_t, const DevPlan *, const uint64_t *, uint32_t *, int) { return hipSuccess; }
+hipError_t launch_rows(hipStream_t, const RowArgs &, int grid, int)
+{
+    g_launches.push_back({"rows", grid});
+    std::unique_lock<std::mutex> lk(g_meet.mu);
+    g_meet.in_step = true;
+    g_meet.cv.notify_all();
+    g_meet.cv.wait_for(lk, std::chrono::seconds(20), [] { return !g_meet.hold_step; });
+    g_meet.cv.wait_for(lk, std::chrono::seconds(2), [] { return g_meet.most >= g_meet.wanted; });
+    return hipSuccess;
+}
 // parts of the library that these checks do not enter
 std::recursive_mutex &hook_mutex() { static std::recursive_mutex m; return m; }
 void hook_forget(ckpt_ctx *) {}
@@ -382,6 +420,67 @@ void check_grids()
     ckpt_destroy(ctx);
 }
 
+uint64_t submit(ckpt_server *sv, int op, void *ptr, uint64_t size, ckpt_image *img)
+{
+    ckpt_request q;
+    memset(&q, 0, sizeof(q));
+    q.op = op;
+    q.n = 1;
+    q.ptrs = &ptr;
+    q.sizes = &size;
+    q.image = img;
+    uint64_t t = 0;
+    CHECK(ckpt_server_submit(sv, &q, &t) == CKPT_OK);
+    return t;
+}
+
+// Restores are copied to the device by every free worker, also while a
+// checkpoint is being packed; a checkpoint's chunks are gathered to the device
+// and copied from there.
+void check_server()
+{
+    const uint64_t bytes = 8 << 20;
+    ckpt_ctx *ctx = context(0);
+    log_memory(ctx, 1 << 30, bytes);
+    g_sel_bytes = g_meet.bytes = bytes;
+    ckpt_image *img = checkpoint(ctx);
+    ckpt_server_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.chunk_bytes = 4096;
+    cfg.staging_budget = 256 << 20;
+    cfg.aux_threads = 4;
+    cfg.step_bytes = 1 << 20;   // several steps: requests join between them
+    ckpt_server *sv = nullptr;
+    CHECK(ckpt_server_create(&cfg, &sv) == CKPT_OK);
+    g_launches.clear();
+    g_meet.hold_step = true;
+    std::vector<uint64_t> tickets{submit(sv, CKPT_REQ_CHECKPOINT, (void *)(1 << 30), bytes, nullptr)};
+    {
+        std::unique_lock<std::mutex> lk(g_meet.mu);
+        CHECK(g_meet.cv.wait_for(lk, std::chrono::seconds(20), [] { return g_meet.in_step; }));
+        g_meet.wanted = 3;
+    }
+    for (int i = 0; i < 3; i++)
+        tickets.push_back(submit(sv, CKPT_REQ_RESTORE, (void *)(1 << 30), bytes, img));
+    {
+        std::lock_guard<std::mutex> lk(g_meet.mu);
+        g_meet.hold_step = false;
+        g_meet.cv.notify_all();
+    }
+    for (uint64_t t : tickets) {
+        ckpt_result r;
+        CHECK(ckpt_server_wait(sv, t, &r) == CKPT_OK && r.status == CKPT_OK);
+        if (r.image)
+            ckpt_image_free(r.image);
+    }
+    g_sel_bytes = 0;
+    CHECK(g_meet.most == 3);
+    CHECK(launched("gather") && !launched("gather_host"));
+    ckpt_server_destroy(sv);
+    ckpt_image_free(img);
+    ckpt_destroy(ctx);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -391,6 +490,8 @@ int main(int argc, char **argv)
         check_dense();
     else if (what == "graph")
         check_graph();
+    else if (what == "server")
+        check_server();
     else if (what == "grids")
         check_grids();
     else if (what == "capture")

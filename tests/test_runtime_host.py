@@ -23,7 +23,7 @@ def runtime_check(tmp_path_factory):
         pytest.skip("no g++ or no HIP headers")
     exe = str(tmp_path_factory.mktemp("runtime") / "runtime_check")
     sources = [os.path.join(ROOT, "tests", "runtime_check.cpp")]
-    sources += [os.path.join(CSRC, f) for f in ("runtime.cpp", "noalloc.cpp", "crc_tables.cpp")]
+    sources += [os.path.join(CSRC, f) for f in ("runtime.cpp", "noalloc.cpp", "server.cpp", "crc_tables.cpp")]
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-w", "-D__HIP_PLATFORM_AMD__",
                     "-D__align__(x)=__attribute__((aligned(x)))", "-DHIP_SYMBOL(x)=((const void*)&(x))",
                     "-I", HIP, "-I", os.path.join(ROOT, "include"), "-I", CSRC, *sources,
@@ -31,7 +31,7 @@ def runtime_check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["dense", "graph", "grids", "capture"])
+@pytest.mark.parametrize("what", ["dense", "graph", "grids", "capture", "server"])
 def test_host_runtime(runtime_check, what):
     r = subprocess.run([runtime_check, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "all checks held" in r.stdout, r.stdout + r.stderr
