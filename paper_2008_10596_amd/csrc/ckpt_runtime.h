@@ -308,6 +308,12 @@ inline uint64_t segment_place(uint64_t bytes, uint64_t slot_bytes, int slot, uin
 {
     return bytes < kSegSlots * slot_bytes ? at : (uint64_t)slot * slot_bytes;
 }
+// Bytes up to which a kernel may store to or load from host memory itself (20
+// us on the link).  While a kernel does, other kernels on the device, of every
+// stream, end only when its accesses in flight do: beside a drain of 240 MiB by
+// one gather, 13 small kernels of another stream came through, the slowest
+// after 4 ms; beside the runtime's copies 280, each within 30 us.
+constexpr uint64_t kLinkDirect = uint64_t(1) << 20;
 // At least n events in ctx->seg_ev.
 int seg_events(ckpt_ctx *ctx, size_t n);
 // The drain a replayed graph may hold: the selected chunks of output i go

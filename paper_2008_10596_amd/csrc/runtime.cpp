@@ -851,10 +851,6 @@ namespace {
 // Workgroups of a gather that stores to host memory: a few saturate the link
 // (64 MiB: 55.5 GB/s with 64, 54.4 with 256, 51.5 with 512 of 1024 threads).
 constexpr int kHostGatherGrid = 64;
-// Dense bytes up to which a drain's pinned buffer is taken before its size is known.
-constexpr uint64_t kEarlyDrain = uint64_t(16) << 20;
-// Bytes of an increment up to which its gather stores to host memory (20 us on the link).
-constexpr uint64_t kSmallDelta = uint64_t(1) << 20;
 
 uint64_t grow(uint64_t x, uint64_t floor) { return std::max<uint64_t>(floor, x + x / 4); }
 }  // namespace
@@ -1239,20 +1235,16 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
 
     hipStream_t ds = ctx->side;      // drain stream: the copies to the host
     hipStream_t gs = incremental ? s : ctx->side;   // the stream the gather runs on
-    // A full checkpoint of at most one segment drains without staging: its
-    // gather stores to the image's pinned memory (55.5 GB/s; the runtime's copy
-    // reaches 56.7 but waits for a gather to staging and a change of streams).
     const uint64_t seg_b = segment_bytes(cfg);
     const uint64_t seg_chunks = seg_b ? std::max<uint64_t>(1, seg_b / C) : 0;
-    bool to_host = direct || (!incremental && !graph_drain && nout == 1 && N <= seg_chunks);
-    // A small one does not wait for its serialized size either: the buffer takes
-    // the dense bytes, and the gather follows the selection at once.  (To
-    // 16 MiB, 0.3 ms on the link: the wait is some 15 us, and an image with
-    // ZERO chunks keeps more pinned memory than it fills -- up to eight times,
-    // above which its bytes, at most 2 MiB, move to a buffer of their size.
-    // Without memory for the dense bytes the drain waits for the size.)
-    bool early = to_host && !direct && !no_drain && N && L.data_bytes <= kEarlyDrain &&
-                       (!cfg.staging_budget || 2 * L.data_bytes <= cfg.staging_budget);
+    // Few bytes drain without staging: their gather stores to the image's
+    // pinned memory.  Where the dense bytes are few it does not wait for the
+    // serialized size either (some 15 us): the buffer takes the dense bytes, no
+    // more than the pool's granule.  Without memory for them the drain waits.
+    // (A drain of 1 MiB: 168 us through staging, 77 so.)
+    bool to_host = direct;
+    bool early = !direct && !incremental && !graph_drain && nout == 1 && !no_drain && N && L.data_bytes <= kLinkDirect &&
+                 (!cfg.staging_budget || 2 * L.data_bytes <= cfg.staging_budget);
     GatherArgs ga;
     memset(&ga, 0, sizeof(ga));
     ga.plan = (const DevPlan *)ctx->d_plan.p;
@@ -1289,33 +1281,28 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
             early = false;
         if (early) {
             ga.out = (uint8_t *)data[0].p;
+            ga.out_host = 1;
             HIP_TRY(launch_gather(ds, ga, kHostGatherGrid));
             if (timing)
                 HIP_TRY(hipEventRecord(ctx->ev[5], ds));
             CKPT_TRY(read_selection(ctx, ds, &P));
-            if (!P.sel_bytes) {
+            if (!P.sel_bytes)
                 data[0].release();
-            } else if (P.sel_bytes <= L.data_bytes / 8) {
-                PinnedBuf fit;
-                if (fit.ensure(P.sel_bytes) == CKPT_OK && fit.cap < data[0].cap) {
-                    memcpy(fit.p, data[0].p, P.sel_bytes);   // the gather is complete
-                    data[0] = std::move(fit);
-                }
-            }
         } else {
             CKPT_TRY(read_selection(ctx, s, &P));
         }
     }
 
     const uint64_t sel_bytes = no_drain ? 0 : P.sel_bytes;
+    // (a small delta holds `s` for less time on the link than staging and a
+    // change of streams take)
+    to_host = to_host || (!graph_drain && nout == 1 && sel_bytes <= kLinkDirect);
+    ga.out_host = to_host ? 1 : 0;
+    const bool ids_by_gather = incremental && sel_bytes && P.sel_count * 8 <= kLinkDirect;
     if (incremental) {
-        // a small delta holds `s` for less time on the link than staging and a
-        // change of streams take
-        to_host = to_host || sel_bytes <= kSmallDelta;
-        ga.out_host = to_host ? 1 : 0;
         CKPT_TRY(ids.ensure(std::max<uint64_t>(P.sel_count, 1) * 8));
         ga.copy[0] = {ctx->d_ids.p, ids.p, P.sel_count * 8};
-        ga.n_copy = 1;
+        ga.n_copy = ids_by_gather ? 1 : 0;
     }
     // A full checkpoint drains in segments of seg_chunks chunks: each
     // segment's gather (on the gather stream, into one of kSegSlots device
@@ -1486,7 +1473,7 @@ int ckpt::run_checkpoint(ckpt_ctx *ctx, hipStream_t s, int mode, const ckpt_imag
     }
     if (incremental) {
         imgs[0]->n_dirty = P.sel_count;
-        if (P.sel_count && !sel_bytes)   // else the gather has copied them
+        if (P.sel_count && !ids_by_gather)
             HIP_TRY(hipMemcpyAsync(ids.p, ctx->d_ids.p, P.sel_count * 8, hipMemcpyDeviceToHost, ds));
         imgs[0]->ids_buf = std::move(ids);
     }
@@ -1611,26 +1598,6 @@ extern "C" int ckpt_restore(ckpt_ctx *ctx, void *stream, const ckpt_image *img, 
 }
 
 namespace {
-// Workgroups of a scatter that reads host memory, of `items` chunks that span
-// `bytes` of memory and `ser` of the link: a few keep the link full and leave
-// it to itself (16 MiB in chunks of 4 KiB: 358 us with 64, 380 - 410 with one
-// per CU), as long as they hold enough loads in flight -- a chunk ahead per
-// wave, at most 4 KiB of it: 64 MiB in chunks of 16 / 64 / 256 / 512 bytes take
-// 11.7 / 2.96 / 1.26 / 1.24 ms with 64 and 3.25 / 1.37 / 1.25 / 1.24 with 256 --
-// and the stores are not what bounds it: an increment that zeroes 4 GiB takes
-// 1.89 ms with 64 and 1.22 with 256, 256 MiB of which 10% are not ZERO 615 and
-// 577 us, 50% 2460 and 2475.
-constexpr int kHostScatterGrid = 64;
-constexpr uint64_t kHostScatterAhead = uint64_t(512) << 10;
-
-int host_scatter_grid(const ckpt_ctx *ctx, uint64_t items, uint64_t bytes, uint64_t ser)
-{
-    const uint64_t waves = (uint64_t)kHostScatterGrid * (ctx->cfg.block_threads / 64);
-    const uint64_t ahead = std::min<uint64_t>(bytes / std::max<uint64_t>(items, 1) / ctx->cfg.waves_per_chunk, 4096);
-    const bool link_bound = ahead * waves >= kHostScatterAhead && ser >= bytes / 2;
-    return link_bound ? std::min(ctx->grid_chunks, kHostScatterGrid) : ctx->grid_chunks;
-}
-
 // The flags of the image (1) or the increment (2) select other than its serialized bytes.
 int bad_selection(uint64_t which, uint64_t found, const ckpt_image *img, const ckpt_image *delta)
 {
@@ -1734,12 +1701,11 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
         }
     } sync_on_error{{s, ctx->side}};
 
-    // Up to one segment, the scatter reads the serialized bytes from the
-    // image's pinned memory itself, verifying as they arrive; more go through
-    // staging, where the runtime's copies are 3% faster on the link.
-    const bool base_direct = n_seg == 1 && img->device == ctx->cfg.device;
+    // Few serialized bytes are read by the scatter from the image's pinned
+    // memory itself; more go through staging (kLinkDirect).
+    const bool base_direct = n_seg == 1 && img->ser_bytes <= kLinkDirect && img->device == ctx->cfg.device;
     const uint64_t nd = delta ? delta->n_dirty : 0;
-    const bool delta_direct = nd && delta->ser_bytes <= seg_b && delta->device == ctx->cfg.device;
+    const bool delta_direct = nd && delta->ser_bytes <= kLinkDirect && delta->device == ctx->cfg.device;
     CKPT_TRY(ctx->d_crc.ensure(std::max<uint64_t>(N, 1) * 4));
     CKPT_TRY(ctx->d_flags.ensure(std::max<uint64_t>(N, 1)));
     CKPT_TRY(ctx->d_bad.ensure((N + 8) / 8 * 8));   // cleared in words
@@ -1765,6 +1731,15 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
             copies.push_back({delta->crc, ctx->d_crc2.p, N * 4});
             copies.push_back({delta->flags, ctx->d_flags2.p, N});
             copies.push_back({delta->ids_buf.p, ctx->d_ids.p, nd * 8});
+        }
+        uint64_t copied = 0;
+        for (const CopySpan &c : copies)
+            copied += c.bytes;
+        if (copied > kLinkDirect) {
+            for (const CopySpan &c : copies)
+                if (c.bytes)
+                    HIP_TRY(hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyHostToDevice, s));
+            copies.clear();
         }
         CKPT_TRY(upload_table(ctx, s, rows, L.off, L.cb, N, nullptr, nullptr, ctx->d_bad.p, (N + 7) / 8 * 8, copies));
     }
@@ -1792,9 +1767,7 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
         if (timing)
             HIP_TRY(hipEventRecord(ctx->ev[1], s));
         a.n_known = N;
-        HIP_TRY(launch_chunks(s, kModeRestore, a,
-                              base_direct ? host_scatter_grid(ctx, N, img->data_bytes, img->ser_bytes) : ctx->grid_chunks,
-                              ctx->cfg.block_threads));
+        HIP_TRY(launch_chunks(s, kModeRestore, a, ctx->grid_chunks, ctx->cfg.block_threads));
     } else if (N) {
         CKPT_TRY(read_selection(ctx, s, &P));
         if (P.sel_bytes != img->ser_bytes)
@@ -1860,10 +1833,7 @@ int ckpt::restore_impl(ckpt_ctx *ctx, void *stream, const ckpt_image *img, const
         b.want_flags = (const uint8_t *)ctx->d_flags2.p;
         b.ids = (const uint64_t *)ctx->d_ids.p;
         b.n_known = nd;
-        const uint64_t spanned = std::min<uint64_t>(nd * img->C, img->data_bytes);   // at most, by the dirty chunks
-        HIP_TRY(launch_chunks(s, kModeRestore, b,
-                              delta_direct ? host_scatter_grid(ctx, nd, spanned, delta->ser_bytes) : ctx->grid_chunks,
-                              ctx->cfg.block_threads));
+        HIP_TRY(launch_chunks(s, kModeRestore, b, ctx->grid_chunks, ctx->cfg.block_threads));
     }
     if (timing)
         HIP_TRY(hipEventRecord(ctx->ev[2], s));

@@ -229,9 +229,14 @@ int prep_request(ckpt_server *sv, Req *r, hipStream_t s, PinnedBuf &up)
     pa.map = r->d_map;
     uint64_t items = (n + kRowTile - 1) / kRowTile + np;
     if (r->op == CKPT_REQ_RESTORE && N) {   // with the stored CRCs and flags, and the bad marks cleared
-        pa.copy[0] = {r->image->crc, r->d_crc, 4 * N};
-        pa.copy[1] = {r->image->flags, r->d_flags, N};
-        pa.n_copy = 2;
+        if (5 * N <= kLinkDirect) {
+            pa.copy[0] = {r->image->crc, r->d_crc, 4 * N};
+            pa.copy[1] = {r->image->flags, r->d_flags, N};
+            pa.n_copy = 2;
+        } else {
+            REQ_HIP(r, hipMemcpyAsync(r->d_crc, r->image->crc, 4 * N, hipMemcpyHostToDevice, s));
+            REQ_HIP(r, hipMemcpyAsync(r->d_flags, r->image->flags, N, hipMemcpyHostToDevice, s));
+        }
         pa.zero = (uint64_t *)r->d_bad;
         pa.zero_words = (N + 7) / 8;
         items = std::max<uint64_t>(items, std::min<uint64_t>(128, N >> 10));

@@ -6,9 +6,10 @@
 //   runtime_check dense     a DENSE view whose staging is gone is refused
 //   runtime_check graph     a captured graph is replayed while its capacities hold
 //   runtime_check server    restores beside a checkpoint; finishes through staging
-//   runtime_check grids     workgroups of a refill from host memory
+//   runtime_check link      what kernels read and write over the host link
 //   runtime_check capture   what an allocation-free call puts into a capture
 // Exit status 0 when every check holds; the first failing check is printed.
+#include <algorithm>
 #include <chrono>
 #include <condition_variable>
 #include <cstdio>
@@ -40,7 +41,10 @@ struct Launch {
     std::string what;
     int grid;
     uint64_t n_known = 0;
+    const void *from = nullptr;   // restore: the serialized bytes
+    uint32_t n_copy = 0;
 };
+uint64_t g_spans = 0;        // most bytes that a table's launch copied
 bool g_capturing = false;    // the caller's streams
 const void *g_copied = nullptr;   // source of the last copy
 struct Launches : std::vector<Launch> {
@@ -125,6 +129,10 @@ hipError_t hipGetSymbolAddress(void **p, const void *s) { *p = const_cast<void *
 namespace ckpt {
 hipError_t launch_prologue(hipStream_t, const PrologueArgs &a, uint64_t)
 {
+    uint64_t n = 0;
+    for (uint32_t i = 0; i < a.n_copy; i++)
+        n += a.copy[i].bytes;
+    g_spans = std::max(g_spans, n);
     *a.plan = *a.up_plan;
     return hipSuccess;
 }
@@ -135,7 +143,7 @@ hipError_t launch_prologue_small(hipStream_t, const PrologueArgs &, const SmallT
 }
 hipError_t launch_chunks(hipStream_t, int mode, const ChunkArgs &a, int grid, int)
 {
-    g_launches.push_back({mode == kModeRestore ? "restore" : mode == kModePack ? "pack" : "hash", grid, a.n_known});
+    g_launches.push_back({mode == kModeRestore ? "restore" : mode == kModePack ? "pack" : "hash", grid, a.n_known, a.staging});
     return hipSuccess;
 }
 hipError_t launch_chunks_table(hipStream_t, int, const ChunkArgs &, const SmallTable &, int grid, int)
@@ -154,7 +162,7 @@ hipError_t launch_select(hipStream_t, const SelArgs &a, uint64_t, bool)
 }
 hipError_t launch_gather(hipStream_t, const GatherArgs &a, int grid)
 {
-    g_launches.push_back({a.out_host ? "gather_host" : "gather", grid});
+    g_launches.push_back({a.out_host ? "gather_host" : "gather", grid, 0, nullptr, a.n_copy});
     return hipSuccess;
 }
 hipError_t launch_pick_u64(hipStream_t, const uint64_t *, const uint64_t *, uint64_t *, uint32_t) { return hipSuccess; }
@@ -353,69 +361,85 @@ void check_capture()
     }
 }
 
-// The grid of a refill of one image of n allocations of `bytes` each, of which
-// `ser` bytes are serialized.
-int refill_grid(uint32_t C, uint32_t block, uint32_t waves, uint64_t n, uint64_t bytes, uint64_t ser)
+// What a drain of n allocations of `bytes` each, of which `ser` bytes are
+// serialized, launches, and then a refill of the image.
+struct Route {
+    bool drain_direct, refill_direct;
+    int refill_grid;
+};
+Route route(uint32_t C, uint64_t n, uint64_t bytes, uint64_t ser)
 {
-    ckpt_config cfg;
-    memset(&cfg, 0, sizeof(cfg));
-    cfg.chunk_bytes = C;
-    cfg.block_threads = block;
-    cfg.waves_per_chunk = waves;
-    ckpt_ctx *ctx = nullptr;
-    CHECK(ckpt_init(&cfg, &ctx) == CKPT_OK);
+    ckpt_ctx *ctx = context(0, C);
     std::vector<void *> dst(n);
     for (uint64_t k = 0; k < n; k++) {
         dst[k] = (void *)((uint64_t(1) << 32) + (bytes + 4096) / 4096 * 4096 * k);
         log_memory(ctx, (uint64_t)dst[k], bytes);
     }
     g_sel_bytes = ser;
+    Route r{};
+    g_launches.clear();
     ckpt_image *img = checkpoint(ctx);
+    CHECK(img->ser_bytes == ser);
+    r.drain_direct = launched("gather_host");
+    CHECK(r.drain_direct != launched("gather") || !ser);
     g_launches.clear();
     CHECK(ckpt_restore(ctx, nullptr, img, nullptr, dst.data(), nullptr, n, nullptr) == CKPT_OK);
     g_sel_bytes = 0;
-    CHECK(g_launches.size() == 1 && g_launches[0].what == "restore");
-    const int grid = g_launches[0].grid;
+    CHECK(g_launches.size() && g_launches[0].what == "restore");
+    r.refill_grid = g_launches[0].grid;
+    r.refill_direct = g_launches[0].from == img->data.p;
     ckpt_image_free(img);
     ckpt_destroy(ctx);
-    return grid;
+    return r;
 }
 
-// Few workgroups where the link bounds a refill, one per CU (256) otherwise.
-void check_grids()
+// Kernels reach over the link for a MiB at most (others wait meanwhile); the
+// rest goes through staging, and refills take the whole chip.
+void check_link()
 {
     const uint64_t M = 1 << 20;
-    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 64 * M) == 64);
-    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 32 * M) == 64);
-    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 32 * M - 16) == 256);   // stores bound it
-    CHECK(refill_grid(4096, 0, 0, 1, 64 * M, 0) == 256);
-    CHECK(refill_grid(512, 0, 0, 1, 64 * M, 64 * M) == 64);
-    CHECK(refill_grid(496, 0, 0, 1, 64 * M, 64 * M) == 256);         // too few bytes in flight
-    CHECK(refill_grid(16, 0, 0, 1, 64 * M, 64 * M) == 256);
-    CHECK(refill_grid(4096, 64, 0, 1, 64 * M, 64 * M) == 256);
-    CHECK(refill_grid(4096, 256, 0, 1, 64 * M, 64 * M) == 64);
-    CHECK(refill_grid(4096, 0, 16, 1, 64 * M, 64 * M) == 256);
-    CHECK(refill_grid(65536, 0, 0, 1000, 100, 112000) == 256);       // short chunks whatever C is
-    CHECK(refill_grid(65536, 0, 0, 1000, 1000, 1008000) == 64);
-    // an increment that zeroes memory
-    ckpt_ctx *ctx = context(0);
+    for (uint32_t C : {16, 4096, 65536}) {
+        for (uint64_t ser : {uint64_t(16), M}) {
+            const Route r = route(C, 1, M, ser);
+            CHECK(r.drain_direct && r.refill_direct && r.refill_grid == 256);
+        }
+        for (uint64_t bytes : {M + 16, 9 * M, 16 * M, 240 * M}) {
+            if (bytes / C > 4 * M)
+                continue;
+            Route r = route(C, 1, bytes, bytes);
+            CHECK(!r.drain_direct && !r.refill_direct && r.refill_grid == 256);
+            r = route(C, 1, bytes, M / 2);
+            CHECK(r.drain_direct && r.refill_direct && r.refill_grid == 256);
+        }
+    }
+    // more chunks than a segment has, and few bytes
+    CHECK(route(65536, 5000, 100, 5000 * 112).drain_direct);
+    // an increment's ids and bytes, and its refill
+    ckpt_ctx *ctx = context(0, 16);
     log_memory(ctx, 1 << 20, 64 * M);
     g_sel_bytes = 64 * M;
     ckpt_image *base = checkpoint(ctx);
-    for (uint64_t ser : {uint64_t(0), M, 16 * M}) {
-        g_sel_bytes = ser;
-        g_sel_count = 4096;
-        ckpt_image *delta = checkpoint(ctx, CKPT_INCREMENTAL, base);
-        for (uint64_t i = 0; i < 4096; i++)   // no kernel has written the ids
-            ((uint64_t *)delta->ids_buf.p)[i] = i;
-        void *dst = (void *)(1 << 20);
-        g_launches.clear();
-        CHECK(ckpt_restore(ctx, nullptr, base, delta, &dst, nullptr, 1, nullptr) == CKPT_OK);
-        CHECK(g_launches.size() == 2 && g_launches[0].grid == 64);
-        CHECK(g_launches[1].grid == (ser == 16 * M ? 64 : 256));
-        ckpt_image_free(delta);
+    for (uint64_t ser : {uint64_t(0), M, M + 16}) {
+        for (uint64_t count : {M / 8, M / 8 + 1}) {
+            g_sel_bytes = ser;
+            g_sel_count = count;
+            g_launches.clear();
+            ckpt_image *delta = checkpoint(ctx, CKPT_INCREMENTAL, base);
+            CHECK(launched("gather_host") == (ser == M) && launched("gather") == (ser > M));
+            if (ser)
+                CHECK(g_launches.back().n_copy == (count == M / 8 ? 1 : 0));
+            for (uint64_t i = 0; i < count; i++)   // no kernel has written the ids
+                ((uint64_t *)delta->ids_buf.p)[i] = i;
+            void *dst = (void *)(1 << 20);
+            g_launches.clear();
+            CHECK(ckpt_restore(ctx, nullptr, base, delta, &dst, nullptr, 1, nullptr) == CKPT_OK);
+            CHECK(g_launches.size() == 2 && g_launches[0].from != base->data.p && g_launches[1].grid == 256);
+            CHECK((g_launches[1].from == delta->data.p) == (ser <= M));
+            ckpt_image_free(delta);
+        }
     }
     g_sel_bytes = g_sel_count = 0;
+    CHECK(g_spans <= M);
     ckpt_image_free(base);
     ckpt_destroy(ctx);
 }
@@ -492,8 +516,8 @@ int main(int argc, char **argv)
         check_graph();
     else if (what == "server")
         check_server();
-    else if (what == "grids")
-        check_grids();
+    else if (what == "link")
+        check_link();
     else if (what == "capture")
         check_capture();
     else

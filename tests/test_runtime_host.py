@@ -31,7 +31,7 @@ def runtime_check(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["dense", "graph", "grids", "capture", "server"])
+@pytest.mark.parametrize("what", ["dense", "graph", "link", "capture", "server"])
 def test_host_runtime(runtime_check, what):
     r = subprocess.run([runtime_check, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "all checks held" in r.stdout, r.stdout + r.stderr
