@@ -236,16 +236,6 @@ def _np_view(p, nbytes, dtype, image):
 
 # ---- images ---------------------------------------------------------------
 
-class DeviceAddress(int):
-    """The address of device memory that an image holds or points to: keeps the
-    image while it is in use (in an array interface, say)."""
-
-    def __new__(cls, value, image):
-        self = super().__new__(cls, value)
-        self._image = image
-        return self
-
-
 class Image:
     """Owns one ckpt_image; frees it on close() / garbage collection.  owner:
     the context in whose staging the dense image lies (CKPT_NO_DRAIN), which
@@ -307,11 +297,12 @@ class Image:
 
     @property
     def dense_ptr(self):
-        """(device address, bytes).  The address keeps the image and its context;
-        with a context that was closed, or whose staging has been replaced by a
-        larger one, the image's dense copy is gone and this raises."""
-        p, n = self.view(CKPT_SEC_DENSE)
-        return DeviceAddress(p, self), n
+        """(device address, bytes): valid while the image is open, which keeps its
+        context.  Raises when the memory is gone: its context was closed, or has
+        replaced its staging by a larger one.  (The address is a plain int, which
+        keeps nothing: torch never lets go of the data tuple of an array
+        interface, so an address that kept the image would keep it for good.)"""
+        return self.view(CKPT_SEC_DENSE)
 
     def serialize(self):
         need = ctypes.c_size_t()
