@@ -252,9 +252,9 @@ struct GatherArgs {
     const uint64_t *out_addr;
     const uint32_t *row_out;
     const uint64_t *out_chunk0;
-    // copied to host memory beside the chunks: an increment's ids; CRCs and flags
+    // copied to host memory beside the chunks: an increment's ids
     uint32_t n_copy;
-    CopySpan copy[2];
+    CopySpan copy[1];
 };
 
 // Launch wrappers (kernels.hip).  All return the hipError_t of the launch.

@@ -137,8 +137,10 @@ extern "C" int ckpt_checkpoint_noalloc(ckpt_ctx *ctx, void *stream, int mode, co
     bool captured = false;
     if (s) {   // the null stream is not captured
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        HIP_TRY(hipStreamIsCapturing(s, &st));
-        captured = st != hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) == hipSuccess)
+            captured = st != hipStreamCaptureStatusNone;
+        else
+            (void)hipGetLastError();   // a legacy handle, which is not captured either
     }
     SmallTable t;
     const bool small = n && n <= kRowTile && !captured;
