@@ -431,6 +431,11 @@ __global__ void k_chunk_map(const DevPlan *plan, const uint64_t *__restrict__ cb
 // window of memory stays narrow (random 4 KiB chunks: 128 per tile 1.64 ms for
 // 4 GiB, 64 1.52, 32 1.51; the 1.6 GB batch 635 / 612 / 602 us).
 constexpr int kTile = 32;
+// Of chunks of at most 2 KiB: as many bytes per tile, since a tile's barrier and
+// its chunks' latency cost the same whatever their size.  (512 MiB, tiles of 32
+// / 64: random chunks of 1 KiB 0.357 / 0.309 ms, all ZERO 0.251 / 0.161, and
+// 0.842 / 0.480 at 256 bytes; at 4 KiB both take the same.)
+constexpr int kShortTile = 64;
 constexpr int kRowsTile = 64;   // of the serving loop's launches
 
 struct Desc {
@@ -1310,12 +1315,12 @@ __device__ __forceinline__ void chunks(const ChunkArgs &a, const SmallTable *tab
     __shared__ __attribute__((aligned(16))) uint32_t tabs[kRepWords];
     // two descriptor tiles: the first wave loads the next tile's descriptors
     // while the workgroup works on the current one
-    constexpr int kDescTile = FORM == kFormQuad ? kQuadTile : kTile;
+    constexpr int kDescTile = FORM == kFormQuad ? kQuadTile : FORM == kFormSmall ? kShortTile : kTile;
     __shared__ Desc desc[2][kDescTile];
     // results of the last 2 * kOutTiles tiles: a tile's go to the device arrays
     // when it is done, kOutTiles tiles' to the host at a time
     constexpr int kOutTile = MODE == kModeRestore ? 1 : kDescTile;
-    constexpr int kOutTiles = MODE == kModeRestore ? 1 : kOutResults / kDescTile;
+    constexpr int kOutTiles = MODE == kModeRestore ? 1 : kOutResults / (FORM == kFormSmall ? kTile : kDescTile);
     __shared__ __attribute__((aligned(16))) uint32_t s_crc[2 * kOutTiles][kOutTile];
     __shared__ __attribute__((aligned(16))) uint8_t s_flags[2 * kOutTiles][kOutTile];
     __shared__ uint64_t s_done[2 * kOutTiles];   // the tiles
@@ -1340,12 +1345,13 @@ __device__ __forceinline__ void chunks(const ChunkArgs &a, const SmallTable *tab
     // takes the tile after the next while the workgroup works on the current
     // one), so the grid sweeps the memory in order and a workgroup whose tiles
     // are cheap (ZERO chunks, read only) takes more of them.
-    // A tile holds at most kDescTile chunks and, for large chunks, about
-    // 1 MiB (but at least one chunk per group of waves), so that a launch
-    // has many tiles per workgroup and its last tiles end close together; and
-    // few enough for two tiles per workgroup, down to one chunk per group of
-    // waves: 2350 chunks in tiles of 64 kept 37 of 256 workgroups busy.  (Four
-    // per workgroup: hash-only of 131072 chunks 139 us, two 121, one 146.)
+    // A tile holds at most kDescTile chunks (in the small form kTile of more
+    // than 2 KiB) and, for large chunks, about 1 MiB (but at least one chunk per
+    // group of waves), so that a launch has many tiles per workgroup and its
+    // last tiles end close together; and few enough for two tiles per
+    // workgroup, down to one chunk per group of waves: 2350 chunks in tiles of
+    // 64 kept 37 of 256 workgroups busy.  (Four per workgroup: hash-only of
+    // 131072 chunks 139 us, two 121, one 146.)
     int tile = kDescTile < (int)blockDim.x ? kDescTile : (int)blockDim.x;
     const int least = FORM == kFormQuad ? kQuadRows * nwaves : groups;
     if (FORM == kFormWave || FORM == kFormLong) {
@@ -1353,6 +1359,8 @@ __device__ __forceinline__ void chunks(const ChunkArgs &a, const SmallTable *tab
         const int want = by_bytes > groups ? by_bytes : groups;
         tile = want < tile ? want : tile;
     }
+    if (FORM == kFormSmall && r_full > 2)
+        tile = kTile < tile ? kTile : tile;
     int tile_log = 31 - __builtin_clz(tile);   // a power of two (as `least` is)
     while ((1 << tile_log) > least && ((uint64_t)2 * gridDim.x << tile_log) > M)
         tile_log--;

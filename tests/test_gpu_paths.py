@@ -575,3 +575,35 @@ def test_gather_of_short_chunks_under_a_large_chunk_size(C, n, longest):
             best.append(min(times))
     log("  increment of %d short allocations: %.0f us, with 4 KiB chunks %.0f us" % (len(short), best[1] * 1e6, best[0] * 1e6))
     assert best[1] < 5 * best[0] + 200e-6
+
+
+@pytest.mark.parametrize("C", [16, 1008, 1024, 1040, 2048, 2064])
+@pytest.mark.parametrize("zero", [0, 1])
+def test_tiles_of_short_chunks(C, zero):
+    """Chunks on both sides of the sizes at which the tile changes, in numbers
+    around two tiles of 32 and of 64 for every workgroup, and many more than a
+    group of results; random, and ZERO but for a chunk here and there: snapshot,
+    refill and the allocation-free pass are the oracle's."""
+    grid = torch.cuda.get_device_properties(0).multi_processor_count
+    for n in (1, 63, 65, 64 * grid - 1, 64 * grid + 1, 128 * grid, 128 * grid + 33, 200 * grid + 7):
+        t = random_allocs([n * C - min(C - 1, 5)], seed=98 + n)[0]
+        if zero:
+            keep = t[:: 37 * C].clone()
+            t.zero_()
+            t[:: 37 * C] = keep
+        ref = O.checkpoint([host(t)], C)
+        ctx = K.Context(chunk_bytes=C)
+        ctx.register(t)
+        img = ctx.checkpoint()
+        check_full(img, ref, [t], C)
+        dst = torch.full_like(t, 0x5A)
+        assert ctx.restore(img, [dst])[0] == K.CKPT_OK and torch.equal(dst, t)
+        N, D = ctx.noalloc_sizes()
+        dense = torch.zeros(D, dtype=torch.uint8, device="cuda")
+        crc = torch.zeros(N, dtype=torch.int32, device="cuda")
+        fl = torch.zeros(N, dtype=torch.uint8, device="cuda")
+        ctx.checkpoint_noalloc(crc, fl, dense=dense)
+        assert np.array_equal(host(crc).view(np.uint32), ref["crc"]) and np.array_equal(host(fl), ref["flags"])
+        assert np.array_equal(host(dense)[:t.numel()], host(t))
+        img.close()
+        ctx.close()
